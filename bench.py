@@ -34,8 +34,7 @@ FP32_MFMA_PEAK_TFLOPS = 157.3
 # this build does not emit: 256 CUs x 4 SIMDs x 16 lanes x 2 flop x 2.4 GHz
 FP32_VALU_PEAK_TFLOPS = 78.6
 BF16_MFMA_PEAK_TFLOPS = 2500.0
-KERNEL_SOURCES = {"edge_prologue_kernel": "k_radial.hip", "radial_bwd_kernel": "k_radial.hip",
-                  "tpr_fwd_kernel": "k_tpr.hip", "tpr_bwd_kernel": "k_tpr.hip", "linear_kernel": "k_node.hip",
+KERNEL_SOURCES = {"edge_prologue_kernel": "k_radial.hip", "tpr_fwd_kernel": "k_tpr.hip", "tpr_bwd_kernel": "k_tpr.hip", "linear_kernel": "k_node.hip",
                   "l0_gather_kernel": "k_layer0.hip", "l0_edge_bwd_kernel": "k_layer0.hip",
                   "sender_sum_kernel": "k_sender.hip"}
 # the edge-product kernels: dense radial products (MFMA) plus the CG
@@ -74,7 +73,7 @@ def edge_product_work(layer, K, E, N, backward):
     """Algorithmic work of one edge-product launch (one layer in per-edge
     form), per the cost model: per edge the last radial layer 2*64*P*K flop
     (dense, MFMA) and the CG contraction 2K(nnz + mid) flop (VALU), the
-    backward twice the forward (R recomputed and dE/da3; the CG VJP).
+    backward twice the forward (R recomputed and dR/dr; the CG VJP).
     Compulsory HBM bytes of the fused form: E*16 + N*(D_in + mid)*K*4
     (doubled for the backward).  Returns (mfma_flops, valu_flops,
     compulsory_bytes)."""
@@ -83,27 +82,22 @@ def edge_product_work(layer, K, E, N, backward):
     return (f * E * 2 * 64 * P * K, f * E * 2 * K * (nnz + mid), f * (E * 16 + N * (din + mid) * K * 4))
 
 
-def hbm_class_bytes(name, model, N, E, l0_factored, n_species, presplit):
+def hbm_class_bytes(name, model, N, E, l0_factored, n_species, parts):
     """Compulsory bytes of every launch of an HBM-priced kernel class in one
     step, summed: each input and output the kernel must move, once."""
-    K, nb, layers = model["K"], model["n_bessel"], model["layers"]
-    n_ct = K // 16
+    K, layers = model["K"], model["layers"]
     ki = 64 * n_species
     tot = 0.0
     for t, L in enumerate(layers):
         mid, din = L["mid"], L["din"]
         fact = l0_factored and t == 0
-        a3b = 384 if (presplit and din == 4 and not fact) else 256
+        a3b = 384 if (parts and not fact) else 256
         if name == "l0_gather_kernel" and fact:
             tot += E * (256 + 64 + 4) + (N + 1) * 4 + N * 16 * ki * 4
         elif name == "l0_edge_bwd_kernel" and fact:
-            tot += N * 16 * ki * 4 + E * (256 + 64 + 4) + E * (256 + 64)
+            tot += N * 16 * ki * 4 + E * (2 * 256 + 64 + 4) + E * 64
         elif name == "edge_prologue_kernel":
-            tot += E * ((12 + 8 + 32 + 64 + nb * 4) if t == 0 else 0) + E * a3b
-        elif name == "radial_bwd_kernel":
-            acc = t < len(layers) - 1
-            parts = 1 if fact else n_ct
-            tot += E * (nb * 4 + parts * (256 + 64) + 64 * (1 + acc) + nb * 4 * (1 + acc))
+            tot += E * ((12 + 8 + 32 + 64) if t == 0 else 0) + E * 2 * a3b
         elif name == "sender_sum_kernel" and t > 0:
             tot += E * (din * K * 4 + 4) + N * din * K * 4
     return tot
@@ -241,8 +235,7 @@ class Arm:
         B = self.B
         model = layer_shapes(self.params)
         l0_factored = B.mace_layer0_form(self.g.handle, -1) == B.MACE_L0_FACTORED
-        presplit = (self.prec != B.MACE_BF16_RADIAL
-                    and B.mace_fp32_products(self.g.handle, -1) == B.MACE_PRODUCTS_SPLIT_BF16)
+        parts = B.mace_fp32_products(self.g.handle, -1) != B.MACE_PRODUCTS_FP32
         per_launch = k_launches / steps
         avg_ms = k_ms / max(k_launches, 1)
         if kname in EDGE_PRODUCT:
@@ -266,7 +259,7 @@ class Arm:
                                              + vf / (FP32_VALU_PEAK_TFLOPS * 1e12)) / (avg_ms * 1e-3), 4),
                     "compulsory_bytes_per_launch": int(cb)}
         else:
-            byts = hbm_class_bytes(kname, model, self.N, self.E, l0_factored, self.params["n_species"], presplit)
+            byts = hbm_class_bytes(kname, model, self.N, self.E, l0_factored, self.params["n_species"], parts)
             byts /= max(per_launch, 1)
             gbs = byts / (avg_ms * 1e-3) / 1e9
             roof = {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",

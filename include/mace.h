@@ -46,8 +46,9 @@ typedef enum {
                              the outputs then hold non-finite values) */
   MACE_BF16_RADIAL = 3,   /* MACE_BF16_LINEAR, and the last layer of the radial
                              MLP (the P*K-wide one) on BF16 operands with FP32
-                             accumulation: R = bf16(a3) bf16(W) forward and
-                             dE/da3 = bf16(dE/dR) bf16(W)^T backward */
+                             accumulation: R = bf16(a3) bf16(W) forward, and
+                             backward dE/dr = sum dE/dR dR/dr with dR/dr =
+                             (da3/dr to 16 significand bits) bf16(W) */
   MACE_FP64 = 4           /* debug precision: every step in FP64 on the vector
                              units (plain kernels, not tuned for speed), every
                              layer in per-edge form; positions, node energies

@@ -175,15 +175,17 @@ struct Buffers {
       *snd_perm = nullptr, *graph_off = nullptr, *quad_node = nullptr, *quad_species = nullptr,
       *quad_node8 = nullptr, *quad_species8 = nullptr;
   double4* shift = nullptr;
-  float *Y = nullptr, *rbf = nullptr;
-  std::vector<float*> a3;   // per layer: [E][64] last radial hidden layer
-  std::vector<unsigned short*> a3x;   // per layer: its three bfloat16 parts [E][3][64] (split-BF16 products)
+  float* Y = nullptr;
+  // per layer: the last radial hidden layer a3 and da3/dr, FP32 [E][64], or
+  // their three bfloat16 parts [E][3][64] where the layer's edge products take
+  // bfloat16 operands (one buffer, sized for the parts)
+  std::vector<float*> a3, t3;
   std::vector<float*> A, hin, ht;
   float *hlast = nullptr, *sc = nullptr, *At = nullptr, *Apre = nullptr, *B = nullptr;
   // backward
   float *dh0 = nullptr, *dh1 = nullptr, *dB = nullptr, *dA = nullptr, *dApre = nullptr, *dAt = nullptr,
-        *dY = nullptr, *de = nullptr, *Q = nullptr, *dht = nullptr;
-  float *da3p = nullptr, *dYp = nullptr;   // per-channel-tile partials [K/16][E][64], [K/16][E][16]
+        *Q = nullptr, *dht = nullptr;
+  float* dYp = nullptr;   // gradient rows [T K/16][E][16]: dE/dr and dE/dY[1..15] per layer and channel tile
   float *U0 = nullptr, *gU0 = nullptr;     // factorised first layer: U and dE/dU, [N][16][l0_ki]
   int* snd_z = nullptr;                    // [E] species of each edge's sender
   float4* g = nullptr;
@@ -201,7 +203,6 @@ int64_t stress_chunk_bound(int64_t E, int G) { return G + E / kStressChunk + 1; 
 
 void carve(const Model& m, int64_t N, int64_t E, int G, Carver& c, Buffers& b) {
   const int64_t K = m.d.K, S = m.d.n_species, T = m.d.n_layers;
-  const int nb = m.d.n_bessel;
   b.w = c.take<float>(m.total_ext);
   b.wT = c.take<float>(m.total_ext);
   b.wbf = c.take<unsigned short>(m.total);
@@ -223,16 +224,15 @@ void carve(const Model& m, int64_t N, int64_t E, int G, Carver& c, Buffers& b) {
   b.quad_species8 = c.take<int>(nt);
   b.shift = c.take<double4>(std::max<int64_t>(E, 1));
   b.Y = c.take<float>(std::max<int64_t>(E, 1) * 16);
-  b.rbf = c.take<float>(std::max<int64_t>(E, 1) * nb);
   b.a3.resize(T);
-  b.a3x.resize(T);
+  b.t3.resize(T);
   b.A.resize(T);
   b.hin.assign(T, nullptr);
   b.ht.assign(T, nullptr);
   for (int t = 0; t < T; ++t) {
     const LayerPlan& L = m.layers[t];
-    b.a3[t] = c.take<float>(std::max<int64_t>(E, 1) * 64);
-    b.a3x[t] = c.take<unsigned short>(std::max<int64_t>(E, 1) * 3 * 64);
+    b.a3[t] = c.take<float>(std::max<int64_t>(E, 1) * 96);
+    b.t3[t] = c.take<float>(std::max<int64_t>(E, 1) * 96);
     b.A[t] = c.take<float>(N * 16 * K);
     if (t > 0) {
       b.hin[t] = c.take<float>(N * L.din * K);
@@ -251,10 +251,7 @@ void carve(const Model& m, int64_t N, int64_t E, int G, Carver& c, Buffers& b) {
   b.dA = c.take<float>(N * 16 * K);
   b.dApre = c.take<float>(N * 16 * K);
   b.dAt = c.take<float>(N * m.max_mid * K);
-  b.dY = c.take<float>(std::max<int64_t>(E, 1) * 16);
-  b.da3p = c.take<float>((K / 16) * std::max<int64_t>(E, 1) * 64);
-  b.dYp = c.take<float>((K / 16) * std::max<int64_t>(E, 1) * 16);
-  b.de = c.take<float>(std::max<int64_t>(E, 1) * nb);
+  b.dYp = c.take<float>(T * (K / 16) * std::max<int64_t>(E, 1) * 16);
   b.Q = c.take<float>(std::max<int64_t>(E, 1) * m.max_din * K);
   b.dht = c.take<float>(N * m.max_din * K);
   b.g = c.take<float4>(std::max<int64_t>(E, 1));
@@ -324,12 +321,12 @@ void carve64(const Model& m, int64_t N, int64_t E, Carver& c, Buffers64& b) {
 
 enum KernelId {
   KID_EDGE_FEATURES = 0, KID_TP_FWD, KID_LINEAR, KID_SYMCON_FWD, KID_READOUT,
-  KID_TP_BWD, KID_RADIAL_BWD, KID_SYMCON_BWD, KID_SENDER_SUM, KID_EDGE_BWD, KID_FORCES, KID_GRAPH_ENERGY,
+  KID_TP_BWD, KID_SYMCON_BWD, KID_SENDER_SUM, KID_EDGE_BWD, KID_FORCES, KID_GRAPH_ENERGY,
   KID_L0_GATHER, KID_L0_BWD, KID_COUNT
 };
 const char* kKernelNames[KID_COUNT] = {
   "edge_prologue_kernel", "tpr_fwd_kernel", "linear_kernel", "symcon_fwd_kernel",
-  "readout_kernel", "tpr_bwd_kernel", "radial_bwd_kernel", "symcon_bwd_kernel", "sender_sum_kernel",
+  "readout_kernel", "tpr_bwd_kernel", "symcon_bwd_kernel", "sender_sum_kernel",
   "edge_vjp_kernel", "forces_kernel", "graph_energy_kernel", "l0_gather_kernel",
   "l0_edge_bwd_kernel"};
 constexpr int kProfPairs = 4096;
@@ -395,24 +392,21 @@ bool l0_auto(const Model& m, int64_t N, int64_t E) {
   return m.l0_ki > 0 && E >= 3 * (int64_t)m.d.n_species * N;
 }
 
-// The edge products of layer t run their last radial layer on split-BF16
-// operands, and both read a3 as the three parts the prologue writes (radial
-// mode 3; the edge-lane backwards, l_h = 1 and 2), or split it per tile (2).
 bool layer_factorised(const mace_graph* h, int t) {
   return t == 0 && h->l0_fact && !h->tp_round && !h->rad_round;
 }
-bool a3_presplit(const mace_graph* h, int t) {
-  return h->radial_split && h->prec != MACE_BF16_RADIAL && h->m.layers[t].lh_max >= 1 && !layer_factorised(h, t);
-}
-int radial_mode(const mace_graph* h, int t) {
-  return h->prec == MACE_BF16_RADIAL ? 1 : (!h->radial_split ? 0 : (a3_presplit(h, t) ? 3 : 2));
-}
+// Operands of the last radial layer inside the edge products: 0 FP32, 1
+// bfloat16, 3 split bfloat16 (FP32-accurate).
+int radial_mode(const mace_graph* h) { return h->prec == MACE_BF16_RADIAL ? 1 : (h->radial_split ? 3 : 0); }
+// The bfloat16 edge products of layer t read a3 and da3/dr as the three parts
+// the prologue writes (part 0 is the bfloat16 rounding).
+bool a3_parts(const mace_graph* h, int t) { return radial_mode(h) != 0 && !layer_factorised(h, t); }
 
 // Every edge product the handle's settings will launch has a kernel instance
 // (checked before anything is enqueued; the launchers check again).
 bool launchable(const mace_graph* h) {
   for (int t = 0; t < h->m.d.n_layers; ++t)
-    if (!layer_factorised(h, t) && !tpr_supported(h->m.layers[t].lh_max, radial_mode(h, t))) return false;
+    if (!layer_factorised(h, t) && !tpr_supported(h->m.layers[t].lh_max, radial_mode(h))) return false;
   return true;
 }
 
@@ -693,9 +687,10 @@ SymW symw(mace_graph* h, int t) {
 }
 
 // Forward pass; keeps every intermediate the backward pass reads.
-// seed_grad: the last layer's readout also stores the backward pass's
-// starting gradient (dE/dh of the last layer's output, in b.dh0).
-void run_forward(mace_graph* h, hipStream_t s, const float* pos, float* eps, bool seed_grad) {
+// for_forces: the prologue also carries da3/dr, and the last layer's readout
+// also stores the backward pass's starting gradient (dE/dh of the last layer's
+// output, in b.dh0).
+void run_forward(mace_graph* h, hipStream_t s, const float* pos, float* eps, bool for_forces) {
   const Model& m = h->m;
   Buffers& b = h->b;
   const int N = (int)h->N, E = (int)h->E, K = m.d.K;
@@ -708,14 +703,18 @@ void run_forward(mace_graph* h, hipStream_t s, const float* pos, float* eps, boo
       RadialSet rs;
       rs.n = std::min(kMaxRadialLayers, m.d.n_layers - t0);
       rs.rnd = h->rad_round;
+      rs.tangent = for_forces;
       for (int q = 0; q < rs.n; ++q) {
+        const bool parts = a3_parts(h, t0 + q);
         rs.W[q] = b.w + m.off.at(std::to_string(t0 + q) + ".radial.0");
         rs.a3[q] = b.a3[t0 + q];
-        rs.a3x[q] = a3_presplit(h, t0 + q) ? b.a3x[t0 + q] : nullptr;
+        rs.t3[q] = b.t3[t0 + q];
+        rs.a3x[q] = parts ? reinterpret_cast<unsigned short*>(b.a3[t0 + q]) : nullptr;
+        rs.t3x[q] = parts ? reinterpret_cast<unsigned short*>(b.t3[t0 + q]) : nullptr;
       }
-      // (a later chunk recomputes the same Y and rbf)
-      launch_edge_prologue(s, E, pos, b.snd, b.rcv, b.shift, m.d.r_cut, m.d.envelope_p, m.d.n_bessel, b.Y, b.rbf,
-                           rs, b.status);
+      // (a later chunk recomputes the same Y)
+      launch_edge_prologue(s, E, pos, b.snd, b.rcv, b.shift, m.d.r_cut, m.d.envelope_p, m.d.n_bessel, b.Y, rs,
+                           b.status);
     }
   }
   if (h->rad_round) {
@@ -764,9 +763,8 @@ void run_forward(mace_graph* h, hipStream_t s, const float* pos, float* eps, boo
       }
       {
         PROF(KID_TP_FWD);
-        const float* a3t = a3_presplit(h, t) ? reinterpret_cast<const float*>(b.a3x[t]) : b.a3[t];
-        (void)launch_tpr_fwd(s, L.lh_max, N, K, b.rcv_off, b.snd, src_map, a3t, wr3 + m.off.at(pre + "radial.3"),
-                       b.Y, src, inv_c, b.At, radial_mode(h, t), h->tp_round);
+        (void)launch_tpr_fwd(s, L.lh_max, N, K, b.rcv_off, b.snd, src_map, b.a3[t], wr3 + m.off.at(pre + "radial.3"),
+                       b.Y, src, inv_c, b.At, radial_mode(h), h->tp_round);
       }
       if (t == 0 && !lowp) {
         run_linear(h, s, h->comb0, largs(h, b.At, b.A[t], nullptr, false, 0));
@@ -801,7 +799,7 @@ void run_forward(mace_graph* h, hipStream_t s, const float* pos, float* eps, boo
       PROF(KID_READOUT);
       launch_readout_fwd(s, N, K, ro, hout, L.dout * K, b.w + m.off.at(pre + "readout.0"),
                          b.w + m.off.at(pre + "readout.1"), m.d.readout_hidden, lowp, ro_acc, eps,
-                         seed_grad ? b.dh0 : nullptr);
+                         for_forces ? b.dh0 : nullptr);
     }
   }
 }
@@ -816,10 +814,10 @@ void run_backward(mace_graph* h, hipStream_t s, const float* pos, float* F, cons
   const float inv_c = (float)(1.0 / m.d.c_norm);
   float* dnext = b.dh0;
   float* dprev = b.dh1;
+  int n_rows = 0;   // gradient rows written so far
   for (int t = T - 1; t >= 0; --t) {
     const LayerPlan& L = m.layers[t];
     const std::string pre = std::to_string(t) + ".";
-    float* hout = L.last ? b.hlast : b.hin[t + 1];
     // dnext already holds dE/d(output of layer t): for the last layer (one
     // scalar component) its forward readout stored it; for a layer below the
     // last, the transposed linear that wrote dnext added that layer's readout
@@ -850,33 +848,25 @@ void run_backward(mace_graph* h, hipStream_t s, const float* pos, float* F, cons
         if (fact) run_linear(h, s, h->l0fT, largs_l0(h, b.dAt, b.gU0, true));
       }
     }
-    int n_part = K / 16;
+    // the layer's gradient rows (dE/dr and dE/dY per edge): one per channel
+    // tile, or whole from the factorised first layer
+    float* rows = b.dYp + (size_t)n_rows * E * 16;
+    n_rows += fact ? 1 : K / 16;
     if (fact) {
-      // dE/da3 and dE/dY per edge, whole (one partial each)
       PROF(KID_L0_BWD);
-      launch_l0_edge_bwd(s, N, m.d.n_species, b.rcv_off, b.snd_z, b.a3[0], b.Y, b.gU0, h->prec == MACE_BF16_RADIAL,
-                         b.da3p, b.dYp);
-      n_part = 1;
+      launch_l0_edge_bwd(s, N, m.d.n_species, b.rcv_off, b.snd_z, b.a3[0], b.t3[0], b.Y, b.gU0,
+                         h->prec == MACE_BF16_RADIAL, rows);
     } else {
       const float* src = t == 0 ? (h->tp_round ? b.sp_round : b.sp_table) : b.ht[t];
       const int* src_map = t == 0 ? b.species : nullptr;
       PROF(KID_TP_BWD);
-      (void)launch_tpr_bwd(s, L.lh_max, N, K, E, b.rcv_off, b.snd, src_map,
-                     a3_presplit(h, t) ? reinterpret_cast<const float*>(b.a3x[t]) : b.a3[t],
+      (void)launch_tpr_bwd(s, L.lh_max, N, K, E, b.rcv_off, b.snd, src_map, b.a3[t], b.t3[t],
                      (h->rad_round ? b.w_round : b.w) + m.off.at(pre + "radial.3"),
-                     b.Y, src, inv_c, b.dAt, b.dYp, t > 0 ? b.Q : nullptr, b.da3p, radial_mode(h, t), h->tp_round);
+                     b.Y, src, inv_c, b.dAt, rows, t > 0 ? b.Q : nullptr, radial_mode(h), h->tp_round);
     }
-    // The edge backward wrote Q and the partials (about 390 MB at K = 128,
-    // more than the last-level cache holds); the sender sum reads Q first
-    // (measured faster than the radial backward first).
     if (t > 0) {
       PROF(KID_SENDER_SUM);
       launch_sender_sum(s, N, L.din, K, b.snd_off, b.snd_perm, b.Q, b.dht);
-    }
-    {
-      PROF(KID_RADIAL_BWD);
-      launch_radial_bwd(s, E, b.rbf, m.d.n_bessel, b.w + m.off.at(pre + "radial.0"), b.da3p, b.dYp, n_part,
-                        b.dY, b.de, t < T - 1, h->rad_round);
     }
     if (t > 0) {
       {
@@ -889,7 +879,7 @@ void run_backward(mace_graph* h, hipStream_t s, const float* pos, float* F, cons
   }
   {
     PROF(KID_EDGE_BWD);
-    launch_edge_vjp(s, E, pos, b.snd, b.rcv, b.shift, m.d.r_cut, m.d.envelope_p, m.d.n_bessel, b.dY, b.de, b.g);
+    launch_edge_vjp(s, E, pos, b.snd, b.rcv, b.shift, b.dYp, n_rows, b.g);
   }
   {
     PROF(KID_FORCES);

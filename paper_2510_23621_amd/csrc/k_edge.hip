@@ -1,4 +1,4 @@
-// Per-edge geometry backward (g_e = dE/dd_e from dE/dY_e and dE/de_e), the
+// Per-edge geometry backward (g_e = dE/dd_e from dE/dY_e and dE/dr_e), the
 // deterministic force assembly F_i = sum_{e: rcv=i} g_e - sum_{e: snd=i} g_e.
 // (The forward geometry runs in the edge prologue of
 // k_radial.hip.)
@@ -6,25 +6,29 @@
 
 namespace mace {
 
-// g = dE/dd per edge from dE/dY and dE/de: one thread per edge, FP64.
+// g = dE/dd per edge from its gradient rows (n_part partials dYp[part][E][16],
+// summed in part order): one thread per edge, FP64.
 __global__ void __launch_bounds__(256) edge_vjp_kernel(int E, const float* __restrict__ pos,
                                                        const int* __restrict__ snd, const int* __restrict__ rcv,
-                                                       const double4* __restrict__ shift, double rc, int p, int nb,
-                                                       const float* __restrict__ dY, const float* __restrict__ de,
+                                                       const double4* __restrict__ shift,
+                                                       const float* __restrict__ dYp, int n_part,
                                                        float4* __restrict__ g) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= E) return;
-  float dyv[16];
-  const float4* dYv = reinterpret_cast<const float4*>(dY + (size_t)e * 16);
+  f4 s[4];
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const float4 x = dYv[v];
-    dyv[4 * v] = x.x;
-    dyv[4 * v + 1] = x.y;
-    dyv[4 * v + 2] = x.z;
-    dyv[4 * v + 3] = x.w;
+  for (int v = 0; v < 4; ++v) s[v] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int q = 0; q < n_part; ++q) {
+    const f4* row = reinterpret_cast<const f4*>(dYp + ((size_t)q * E + e) * 16);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) s[v] += row[v];
   }
-  g[e] = edge_geometry_vjp(e, pos, snd, rcv, shift, rc, p, nb, dyv, de + (size_t)e * nb);
+  float dy[16];
+#pragma unroll
+  for (int m = 0; m < 16; ++m) dy[m] = s[m >> 2][m & 3];
+  g[e] = edge_geometry_vjp(e, pos, snd, rcv, shift, dy[0], dy);
 }
 
 // Per-graph energy of graph gi in FP64, fixed order: strided partial sums,
@@ -152,9 +156,9 @@ void launch_stress(hipStream_t s, int G, int n_chunks, const int2* chunks, const
 }
 
 void launch_edge_vjp(hipStream_t s, int E, const float* pos, const int* snd, const int* rcv, const double4* shift,
-                     double rc, int p, int nb, const float* dY, const float* de, float4* g) {
+                     const float* dYp, int n_part, float4* g) {
   if (E <= 0) return;
-  edge_vjp_kernel<<<(E + 255) / 256, 256, 0, s>>>(E, pos, snd, rcv, shift, rc, p, nb, dY, de, g);
+  edge_vjp_kernel<<<(E + 255) / 256, 256, 0, s>>>(E, pos, snd, rcv, shift, dYp, n_part, g);
 }
 
 void launch_forces(hipStream_t s, int N, const int* rcv_off, const int* snd_off, const int* snd_perm,

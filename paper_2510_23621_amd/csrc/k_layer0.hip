@@ -13,9 +13,9 @@
 // a node-level contraction over S * 64 channels that runs on the channel-mixing
 // linear kernel (where it can be composed with the path-merging and species
 // linears that follow it). The backward pass receives gU = dE/dU from the
-// transposed contraction and returns per edge
-//   dE/da3[e][j] = sum_c gU[i][c][z_e][j] Y[e][c],
-//   dE/dY[e][c]  = sum_j gU[i][c][z_e][j] a3[e][j].
+// transposed contraction and returns per edge, with a3' = da3/dr,
+//   dE/dr[e]    = sum_j a3'[e][j] sum_c gU[i][c][z_e][j] Y[e][c],
+//   dE/dY[e][c] = sum_j gU[i][c][z_e][j] a3[e][j].
 // In the BF16-radial mode a3 enters as its bfloat16 rounding (the weights
 // carry the rounded W3), which is the same product as the per-edge form.
 //
@@ -92,13 +92,13 @@ __global__ void __launch_bounds__(256) l0_gather_kernel(int N, const int* __rest
 }
 
 // Wave w takes the receiver's edges e_beg + w, e_beg + w + 4, ...; it holds
-// gU[i][c][s][lane] for every (s, c) in registers. dE/da3 goes to da3[e][64],
-// dE/dY to dY[e][16] (both overwritten).
+// gU[i][c][s][lane] for every (s, c) in registers. dE/dr goes to dY[e][0] (the
+// l = 0 harmonic has no gradient), dE/dY to dY[e][1..15].
 template <int S, bool RB>
 __global__ void __launch_bounds__(256) l0_edge_bwd_kernel(int N, const int* __restrict__ rcv_off,
                                                           const int* __restrict__ snd_z,
-                                                          const float* __restrict__ a3, const float* __restrict__ Y,
-                                                          const float* __restrict__ gU, float* __restrict__ da3,
+                                                          const float* __restrict__ a3, const float* __restrict__ t3,
+                                                          const float* __restrict__ Y, const float* __restrict__ gU,
                                                           float* __restrict__ dY) {
   constexpr int KI = 64 * S;
   const int i = blockIdx.x;
@@ -113,12 +113,13 @@ __global__ void __launch_bounds__(256) l0_edge_bwd_kernel(int N, const int* __re
   // kL0BwdEdges edges per iteration (e, e + 4, ...), their loads issued together
   for (int e = e_beg + w; e < e_end; e += 4 * kL0BwdEdges) {
     int ee[kL0BwdEdges], z[kL0BwdEdges];
-    float a[kL0BwdEdges], y[kL0BwdEdges][16];
+    float a[kL0BwdEdges], ta[kL0BwdEdges], y[kL0BwdEdges][16];
 #pragma unroll
     for (int q = 0; q < kL0BwdEdges; ++q) {
       ee[q] = min(e + 4 * q, e_end - 1);   // a missing edge repeats the last one and stores nothing
       z[q] = snd_z[ee[q]];
       a[q] = a3[(size_t)ee[q] * 64 + lane];
+      ta[q] = t3[(size_t)ee[q] * 64 + lane];
 #pragma unroll
       for (int v4 = 0; v4 < 4; ++v4) {
         const f4 t = *reinterpret_cast<const f4*>(Y + (size_t)ee[q] * 16 + 4 * v4);
@@ -144,10 +145,10 @@ __global__ void __launch_bounds__(256) l0_edge_bwd_kernel(int N, const int* __re
       float d = 0.f;
 #pragma unroll
       for (int c = 0; c < 16; ++c) d += gs[c] * y[q][c];
-      da3[(size_t)ee[q] * 64 + lane] = d;
       float v[16];
+      v[0] = d * ta[q];
 #pragma unroll
-      for (int c = 0; c < 16; ++c) v[c] = gs[c] * av;
+      for (int c = 1; c < 16; ++c) v[c] = gs[c] * av;
       const float t = wave_reduce_scatter16(v, lane);
       if ((lane & 3) == 0) dY[(size_t)ee[q] * 16 + (lane >> 2)] = t;
     }
@@ -171,12 +172,12 @@ void launch_l0_gather(hipStream_t s, int N, int S, const int* rcv_off, const int
 }
 
 void launch_l0_edge_bwd(hipStream_t s, int N, int S, const int* rcv_off, const int* snd_z, const float* a3,
-                        const float* Y, const float* gU, int rb, float* da3, float* dY) {
+                        const float* t3, const float* Y, const float* gU, int rb, float* dY) {
   if (N <= 0) return;
   auto go = [&](auto SS) {
     constexpr int SV = decltype(SS)::value;
-    if (rb) l0_edge_bwd_kernel<SV, true><<<N, 256, 0, s>>>(N, rcv_off, snd_z, a3, Y, gU, da3, dY);
-    else l0_edge_bwd_kernel<SV, false><<<N, 256, 0, s>>>(N, rcv_off, snd_z, a3, Y, gU, da3, dY);
+    if (rb) l0_edge_bwd_kernel<SV, true><<<N, 256, 0, s>>>(N, rcv_off, snd_z, a3, t3, Y, gU, dY);
+    else l0_edge_bwd_kernel<SV, false><<<N, 256, 0, s>>>(N, rcv_off, snd_z, a3, t3, Y, gU, dY);
   };
   switch (S) {
     case 1: go(std::integral_constant<int, 1>{}); break;

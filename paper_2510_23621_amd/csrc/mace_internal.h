@@ -234,13 +234,45 @@ __host__ __device__ __forceinline__ void bessel_env(T r, double rc, int p, int n
   }
 }
 
-// g = dE/dd of edge e from dE/dY (dy[16]) and dE/de (de[nb]), by forward-mode
-// differentiation (FP64 dual numbers) of the same closed forms with respect to
-// the three components of d.
+// As bessel_env (FP64), with the derivatives de_n/dr:
+//   d sin(n theta)/dr = n (pi/rc) cos(n theta), cos(n theta) by the same recurrence.
+__host__ __device__ __forceinline__ void bessel_env_dr(double r, double rc, int p, int nb, double* e, double* de) {
+  const double pi = 3.14159265358979323846;
+  const double xr = r * (1.0 / rc);
+  double q = 0.5 * p * (p + 1), dq = 0.0;   // the polynomial and its derivative in x
+  for (int j = p - 2; j >= 0; --j) {
+    dq = dq * xr + q;
+    q = q * xr + 0.5 * (j + 1) * (j + 2);
+  }
+  const double om = 1.0 - xr;
+  double env = (om * om) * (om * q);
+  double denv = (om * om) * (om * dq - 3.0 * q) * (1.0 / rc);
+  if (!(xr < 1.0)) env = denv = 0.0;
+  const double c = sqrt(2.0 / rc);
+  const double pre = (c * env) / r;
+  const double dpre = (c * denv - pre) / r;
+  double s1, c1;
+  sincos(r * (pi / rc), &s1, &c1);
+  const double c2 = 2.0 * c1;
+  double sp = 0.0, sn = s1, cp = 1.0, cn = c1;   // sin and cos of (n - 1) theta and n theta for n = 1
+  for (int n = 0; n < nb; ++n) {
+    e[n] = pre * sn;
+    de[n] = dpre * sn + pre * ((n + 1) * (pi / rc) * cn);
+    const double ns = c2 * sn - sp, nc = c2 * cn - cp;
+    sp = sn;
+    sn = ns;
+    cp = cn;
+    cn = nc;
+  }
+}
+
+// g = dE/dd of edge e from dE/dr at a fixed direction (dr) and dE/dY
+// (dy[1..15]; dy[0] is not read), by forward-mode differentiation (FP64 dual
+// numbers) of the harmonics' closed forms with respect to the three components
+// of d.
 __device__ __forceinline__ float4 edge_geometry_vjp(int e, const float* __restrict__ pos,
                                                     const int* __restrict__ snd, const int* __restrict__ rcv,
-                                                    const double4* __restrict__ shift, double rc, int p, int nb,
-                                                    const float* dy, const float* de) {
+                                                    const double4* __restrict__ shift, float dr, const float* dy) {
   using D3 = Dual3<double>;
   const int s = snd[e], r = rcv[e];
   const double4 sh = shift[e];
@@ -251,48 +283,25 @@ __device__ __forceinline__ float4 edge_geometry_vjp(int e, const float* __restri
   const D3 inv = D3(1.0) / rr;
   D3 y[16];
   sh16<D3>(dx * inv, dyv * inv, dz * inv, y);
-  double gx = 0.0, gy = 0.0, gz = 0.0;
+  double gx = (double)dr * rr.x, gy = (double)dr * rr.y, gz = (double)dr * rr.z;
   for (int m = 1; m < 16; ++m) {
     gx += (double)dy[m] * y[m].x;
     gy += (double)dy[m] * y[m].y;
     gz += (double)dy[m] * y[m].z;
-  }
-  // radial basis: the terms of bessel_env, each added as it is formed (no
-  // array indexed by the run-time basis size, which would live in scratch)
-  const D3 xr = rr * (1.0 / rc);
-  D3 q = D3(0.5 * p * (p + 1));
-  for (int j = p - 2; j >= 0; --j) q = q * xr + 0.5 * (j + 1) * (j + 2);
-  const D3 om = D3(1.0) - xr;
-  D3 env = (om * om) * (om * q);
-  if (!lt(xr, 1.0)) env = D3(0.0);
-  const D3 pre = (sqrt(2.0 / rc) * env) / rr;
-  const double pi = 3.14159265358979323846;
-  D3 s1, c1;
-  dsincos(rr * (pi / rc), &s1, &c1);
-  const D3 c2 = 2.0 * c1;
-  D3 sp = D3(0.0), sn = s1;   // the recurrence of bessel_env
-  for (int n = 0; n < nb; ++n) {
-    const D3 en = pre * sn;
-    const double w = de[n];
-    gx += w * en.x;
-    gy += w * en.y;
-    gz += w * en.z;
-    const D3 nx = c2 * sn - sp;
-    sp = sn;
-    sn = nx;
   }
   return make_float4((float)gx, (float)gy, (float)gz, 0.f);
 }
 
 // Geometry of edge e in FP64, rounded to FP32 once: d = (x_snd - x_rcv) +
 // shift, r = |d|, u = d / r; Y[16] (real harmonics of u) and eb[nb] (radial
-// basis times envelope). The periodic shift and the difference of wrapped
+// basis times envelope), with TAN also its derivative in r (tb[nb]). The periodic shift and the difference of wrapped
 // positions would otherwise carry FP32 rounding into every edge.
 // Returns the edge's device status bits: kStatusNonFinite when d is not
 // finite, kStatusZeroLength when r = 0 (coincident atoms); 0 otherwise.
+template <bool TAN>
 __device__ __forceinline__ int edge_geometry(int e, const float* __restrict__ pos, const int* __restrict__ snd,
                                              const int* __restrict__ rcv, const double4* __restrict__ shift,
-                                             double rc, int p, int nb, float* yout, float* ebout) {
+                                             double rc, int p, int nb, float* yout, float* ebout, float* tbout) {
   const int s = snd[e], r = rcv[e];
   const double4 sh = shift[e];
   const double dx = ((double)pos[3 * s + 0] - (double)pos[3 * r + 0]) + sh.x;
@@ -303,9 +312,13 @@ __device__ __forceinline__ int edge_geometry(int e, const float* __restrict__ po
   double y[16];
   sh16<double>(dx * inv, dy * inv, dz * inv, y);
   for (int m = 0; m < 16; ++m) yout[m] = (float)y[m];
-  double eb[16];
-  bessel_env<double>(rr, rc, p, nb, eb);
-  for (int n = 0; n < nb; ++n) ebout[n] = (float)eb[n];
+  double eb[16], tb[16];
+  if constexpr (TAN) bessel_env_dr(rr, rc, p, nb, eb, tb);
+  else bessel_env<double>(rr, rc, p, nb, eb);
+  for (int n = 0; n < nb; ++n) {
+    ebout[n] = (float)eb[n];
+    if constexpr (TAN) tbout[n] = (float)tb[n];
+  }
   return !isfinite(rr) ? kStatusNonFinite : (rr == 0.0 ? kStatusZeroLength : 0);
 }
 
@@ -427,33 +440,31 @@ struct ChainArgs {
 void launch_linear_chain3(hipStream_t s, const ChainArgs& a);
 
 constexpr int kMaxRadialLayers = 4;
-// hidden-layer weights (W0 of the layer, W1 and W2 follow it) and a3 outputs
-// of up to kMaxRadialLayers interaction layers
+// hidden-layer weights (W0 of the layer, W1 and W2 follow it) and outputs of up
+// to kMaxRadialLayers interaction layers: a3, and with tangent set t3 = da3/dr
 struct RadialSet {
   const float* W[kMaxRadialLayers];
-  float* a3[kMaxRadialLayers];
-  // where set, the layer's a3 is written as its three bfloat16 parts instead,
-  // [E][3][64] (part q of edge e at a3x + (3 e + q) 64): the split-BF16 edge
-  // products then read them rather than splitting a3 per channel tile
-  unsigned short* a3x[kMaxRadialLayers];
+  float *a3[kMaxRadialLayers], *t3[kMaxRadialLayers];
+  // where set, the layer's a3 (t3) is written as its three bfloat16 parts
+  // instead, [E][3][64] (part q of edge e at a3x + (3 e + q) 64): the bfloat16
+  // edge products then read them rather than splitting a3 per channel tile
+  unsigned short *a3x[kMaxRadialLayers], *t3x[kMaxRadialLayers];
   int n;
+  bool tangent;
   int rnd;   // precision study: rounding of every hidden layer's input and weights (0 none, 1 bf16, 2 fp16)
 };
 // first interaction layer in factorised form (U, gU: [N][16][64 S], S <= 4)
 void launch_l0_gather(hipStream_t s, int N, int S, const int* rcv_off, const int* snd_z, const float* a3,
                       const float* Y, int rb, float* U);
 void launch_l0_edge_bwd(hipStream_t s, int N, int S, const int* rcv_off, const int* snd_z, const float* a3,
-                        const float* Y, const float* gU, int rb, float* da3, float* dY);
+                        const float* t3, const float* Y, const float* gU, int rb, float* dY);
 constexpr int kL0MaxSpecies = 4;
 void launch_edge_prologue(hipStream_t s, int E, const float* pos, const int* snd, const int* rcv,
-                          const double4* shift, double rc, int p, int nb, float* Y, float* rbf,
-                          const RadialSet& rs, int* status);
+                          const double4* shift, double rc, int p, int nb, float* Y, const RadialSet& rs, int* status);
 // F from the per-edge g; the same launch writes the per-graph energies E from
 // the node energies eps (as launch_graph_energy).
 void launch_forces(hipStream_t s, int N, const int* rcv_off, const int* snd_off, const int* snd_perm,
                    const float4* g, float* F, int G, const int* graph_off, const float* eps, double* E);
-void launch_radial_bwd(hipStream_t s, int E, const float* rbf, int nb, const float* W, const float* da3p,
-                       const float* dYp, int n_part, float* dY, float* de, int accumulate, int rnd);
 // Stress of every graph from the edge gradients g: per-chunk FP64 partials
 // (chunks [beg, end) of at most kStressChunk edges of one graph, graph gi's
 // chunks at chunk_off[gi] .. chunk_off[gi + 1]), then their ordered sum.
@@ -461,20 +472,24 @@ constexpr int kStressChunk = 8192;
 void launch_stress(hipStream_t s, int G, int n_chunks, const int2* chunks, const int* chunk_off, const float* pos,
                    const int* snd, const int* rcv, const double4* shift, const float4* g, const double* inv_vol,
                    double* part, double* stress);
+// g from the edges' gradient rows dYp[part][E][16] (dE/dr in element 0, dE/dY
+// in 1..15), summed over the n_part partials in order
 void launch_edge_vjp(hipStream_t s, int E, const float* pos, const int* snd, const int* rcv, const double4* shift,
-                     double rc, int p, int nb, const float* dY, const float* de, float4* g);
-// Edge-product launchers: radial 0 FP32, 1 BF16, 2 split BF16 (FP32-accurate),
-// 3 split BF16 with a3 pre-split (l_h = 1); tp_round 0/1/2 none/bf16/fp16.
+                     const float* dYp, int n_part, float4* g);
+// Edge-product launchers: radial 0 FP32, 1 BF16, 3 split BF16 (FP32-accurate);
+// in 1 and 3 a3 (and t3) point at the three bfloat16 parts [E][3][64];
+// tp_round 0/1/2 none/bf16/fp16.
 // They return false, enqueuing nothing, for an (l_h, radial mode) without an
 // instance (tpr_supported is false).
 bool tpr_supported(int lh_max, int radial_mode);
 bool launch_tpr_fwd(hipStream_t s, int lh_max, int N, int K, const int* rcv_off, const int* snd,
                     const int* src_map, const float* a3, const float* W3, const float* Y, const float* h,
                     float inv_c, float* At, int radial_mode, int tp_round);
-// As launch_tpr_fwd. The FP32-accurate l_h = 2 backward needs Q (false otherwise).
+// As launch_tpr_fwd; t3 = da3/dr, gradient rows to dYp[K/16][E][16] (dE/dr, then
+// dE/dY[1..15]), the sender gradient to Q unless null.
 bool launch_tpr_bwd(hipStream_t s, int lh_max, int N, int K, int E, const int* rcv_off, const int* snd,
-                    const int* src_map, const float* a3, const float* W3, const float* Y, const float* h,
-                    float inv_c, const float* dAt, float* dYp, float* Q, float* da3p, int radial_mode,
+                    const int* src_map, const float* a3, const float* t3, const float* W3, const float* Y,
+                    const float* h, float inv_c, const float* dAt, float* dYp, float* Q, int radial_mode,
                     int tp_round);
 void launch_sender_sum(hipStream_t s, int N, int C, int K, const int* snd_off, const int* snd_perm,
                        const float* Q, float* out);
