@@ -40,8 +40,11 @@ constexpr int kYPitch = 20;   // Y tile row: 16 floats + 4 (float4-aligned)
 // SIMD.
 template <int LHMAX, bool BWD, int RM = 0>
 struct TprShape {
-  static constexpr int waves = (BWD && LHMAX == 2) ? 4 : 8;
-  static constexpr int per_simd = BWD ? (LHMAX == 2 ? 1 : 2) : (LHMAX == 2 ? 2 : 4);
+  static constexpr int waves = 8;
+  static constexpr int per_simd = BWD ? 2 : (LHMAX == 2 ? 2 : 4);
+  // waves that share a receiver and its G table, taking its edge tiles in turn
+  // (two where eight tables do not fit beside W3's slice)
+  static constexpr int share = (BWD && LHMAX == 2 && RM != 1) ? 2 : 1;
   static constexpr int blocks_per_cu = 4 * per_simd / waves;
 };
 
@@ -515,16 +518,6 @@ tpr_fwd_kernel(
 // values equal the last valid lane's, so they store the same values to the same
 // rows and the stores need no branch.
 
-// sender rows (channels kb .. kb + 3) and harmonics of the lane's edge
-template <int DIN>
-__device__ __forceinline__ void el_load_hy(f4* hv, f4* y4, int src, int e, int kb, const float* __restrict__ h,
-                                           const float* __restrict__ Y, int K) {
-#pragma unroll
-  for (int c = 0; c < DIN; ++c) hv[c] = *reinterpret_cast<const f4*>(h + ((size_t)src * DIN + c) * K + kb);
-#pragma unroll
-  for (int v = 0; v < 4; ++v) y4[v] = reinterpret_cast<const f4*>(Y + (size_t)e * 16)[v];
-}
-
 // The radial operands of one edge (a3 or a3'), per mode: RM 0 the FP32 row,
 // v[q] = a3[e][16 q + 4 g .. +3]; RM 1 and 3 its first NQ bfloat16 parts,
 // x[ks][q] = part q of a3[e][32 ks + 8 g .. +7] ([E][3][64]).
@@ -568,8 +561,8 @@ __device__ __forceinline__ void load_w3_bwd(const float* __restrict__ W3, int K,
   }
 }
 
-constexpr int kRingR = 3;    // W3 operand sets in flight in the radial products
-constexpr int kRingG = 6;    // G-table entries in flight (one coupling pair each)
+constexpr int kRingR = 2;    // W3 operand sets in flight in the radial products
+constexpr int kRingG = 3;    // G-table entries in flight (one coupling pair each)
 
 // R and R' of the paths PA .. PB - 1 in the edge-lane layout. RM 3: six partial
 // products per operand pair, the smallest first. RM 1: bf16(a3) bf16(W3) for R,
@@ -579,14 +572,13 @@ constexpr int kRingG = 6;    // G-table entries in flight (one coupling pair eac
 template <int PA, int PB, int P, int RM, class XA, class XT>
 __device__ __forceinline__ void radial_group(const void* __restrict__ sW, const XA& a, const XT& t, f4* r, f4* rp) {
   const int l = threadIdx.x & 63, g = l >> 4, kk = l & 15;
-#pragma unroll
-  for (int p = 0; p < PB - PA; ++p) r[p] = rp[p] = f4{0.f, 0.f, 0.f, 0.f};
   __builtin_amdgcn_s_setprio(1);
   if constexpr (RM == 0) {
     const float* wb = reinterpret_cast<const float*>(sW) + kk * kWPitch + 4 * g;
 #pragma unroll
     for (int p = PA; p < PB; ++p) {
       __builtin_amdgcn_sched_barrier(0);
+      r[p - PA] = rp[p - PA] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const f4 b = *reinterpret_cast<const f4*>(wb + p * 16 * kWPitch + 16 * q);
@@ -617,7 +609,7 @@ __device__ __forceinline__ void radial_group(const void* __restrict__ sW, const 
 #pragma unroll
       for (int q = 0; q < NB; ++q) b[q] = ring[(f - F0) % kRingR][q];
       if constexpr (f + kRingR < F1) w_at(f + kRingR, ring[(f - F0) % kRingR]);
-      f4 u = r[p], v = rp[p];
+      f4 u = ks == 0 ? f4{0.f, 0.f, 0.f, 0.f} : r[p], v = ks == 0 ? f4{0.f, 0.f, 0.f, 0.f} : rp[p];
       if constexpr (RM == 1) {
         v = mfma_bf16(b[0], t.x[ks][1], v);
         u = mfma_bf16(b[0], a.x[ks][0], u);
@@ -630,6 +622,9 @@ __device__ __forceinline__ void radial_group(const void* __restrict__ sW, const 
           v = mfma_bf16(b[ib[n]], t.x[ks][ia[n]], v);
         }
       }
+      // both products stay in this step (left free, the compiler moves those of
+      // R', whose use comes later, behind all of R's and keeps every operand set)
+      __asm__ volatile("" : "+v"(u), "+v"(v));
       r[p] = u;
       rp[p] = v;
     });
@@ -639,99 +634,118 @@ __device__ __forceinline__ void radial_group(const void* __restrict__ sW, const 
 
 // G_p of receiver i for channel 16 ct + l%16, path by path (only the path's own
 // dE/dAt values live); the four lane groups compute the same values and the
-// first one stores: sg[pair][channel]
-template <int LHMAX>
-__device__ __forceinline__ void build_g(const float* __restrict__ gsrc, int K, float inv_c, float* __restrict__ sg) {
+// first one stores: sg[pair][channel]. Wave ws of SHARE takes every SHARE-th path.
+template <int LHMAX, int SHARE>
+__device__ __forceinline__ void build_g(const float* __restrict__ gsrc, int K, float inv_c, int ws,
+                                        float* __restrict__ sg) {
   const int l = threadIdx.x & 63, g = l >> 4, kk = l & 15;
-  for_paths<LHMAX>([&](auto tag) {
-    using T = decltype(tag);
-    using C = mt::CG<T::lh, T::ly, T::lo>;
-    constexpr int goff = PathPairOffset<T::index>::value;
-    float gv[2 * T::lo + 1];
+  static_for<0, SHARE>([&](auto WS) {
+    if (SHARE > 1 && ws != decltype(WS)::value) return;
+    for_paths<LHMAX>([&](auto tag) {
+      using T = decltype(tag);
+      if constexpr (T::index % SHARE == decltype(WS)::value) {
+        using C = mt::CG<T::lh, T::ly, T::lo>;
+        constexpr int goff = PathPairOffset<T::index>::value;
+        float gv[2 * T::lo + 1];
 #pragma unroll
-    for (int m = 0; m < 2 * T::lo + 1; ++m) gv[m] = gsrc[(size_t)(T::offset + m) * K + kk] * inv_c;
-    float Gp[C::npair];
+        for (int m = 0; m < 2 * T::lo + 1; ++m) gv[m] = gsrc[(size_t)(T::offset + m) * K + kk] * inv_c;
+        float Gp[C::npair];
 #pragma unroll
-    for (int u = 0; u < C::npair; ++u) Gp[u] = 0.f;
-    C::each_p([&](int m1, int m2, int m3, float cg, int pi) { Gp[pi] += cg * gv[m3]; });
-    if (g == 0) {
+        for (int u = 0; u < C::npair; ++u) Gp[u] = 0.f;
+        C::each_p([&](int m1, int m2, int m3, float cg, int pi) { Gp[pi] += cg * gv[m3]; });
+        if (g == 0) {
 #pragma unroll
-      for (int u = 0; u < C::npair; ++u) sg[(goff + u) * 16 + kk] = Gp[u];
-    }
+          for (int u = 0; u < C::npair; ++u) sg[(goff + u) * 16 + kk] = Gp[u];
+        }
+      }
+    });
   });
 }
 
-// RND: the precision study's rounding of R (rnd: its format); R' is that of
-// the unrounded R, gradients passing through the rounding unchanged.
+// Wait until every one of the SHARE waves of a group has come here as often as
+// this one (cnt: their arrivals, in LDS; due: the count to wait for). All waves
+// of a group are resident in the block and take the same receivers, so each
+// makes the same number of arrivals and the wait ends. For one wave, only the
+// order of its own LDS accesses.
+template <int SHARE>
+__device__ __forceinline__ void group_sync(int* cnt, int& due) {
+  if constexpr (SHARE == 1) {
+    __builtin_amdgcn_wave_barrier();
+  } else {
+    due += SHARE;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    if ((threadIdx.x & 63) == 0) __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    while (__hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < due) __builtin_amdgcn_s_sleep(1);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  }
+}
+
+// RND: the precision study's rounding of R (0 none, 1 bfloat16, 2 binary16; a
+// template value, since a branch on it would split the tile); R' is that of the
+// unrounded R, gradients passing through the rounding unchanged.
 // FIRST: the first layer, whose sender features are rows of the species table
 // (through src_map) and take no gradient; otherwise they are the senders' own
 // rows of h and Q is written.
-template <int LHMAX, int RM, bool RND, bool FIRST, int NW = TprShape<LHMAX, true, RM>::waves>
+template <int LHMAX, int RM, int RND, bool FIRST, int NW = TprShape<LHMAX, true, RM>::waves>
 __global__ void __launch_bounds__(64 * NW)
 __attribute__((amdgpu_waves_per_eu(TprShape<LHMAX, true, RM>::per_simd, TprShape<LHMAX, true, RM>::per_simd)))
 tpr_bwd_kernel(
     int N, int K, int E, const int* __restrict__ rcv_off, const int* __restrict__ snd,
     const int* __restrict__ src_map, const float* __restrict__ a3, const float* __restrict__ t3,
     const float* __restrict__ W3, const float* __restrict__ Y, const float* __restrict__ h, float inv_c,
-    const float* __restrict__ dAt, float* __restrict__ dYp, float* __restrict__ Q, int rnd) {
+    const float* __restrict__ dAt, float* __restrict__ dYp, float* __restrict__ Q) {
   constexpr int P = path_count(LHMAX);
   constexpr int MID = mid_count(LHMAX);
   constexpr int DIN = (LHMAX + 1) * (LHMAX + 1);
   constexpr int NPAIR = PairCount<LHMAX>::value;
   constexpr int kSlice = RM == 0 ? P * 16 * kWPitch * 2 : (RM == 1 ? 1 : 3) * P * 16 * 64;   // 2-byte units
   __shared__ __align__(16) unsigned short sW[kSlice];
-  __shared__ __align__(16) float sG[NW][NPAIR * 16];   // [pair][channel]
+  constexpr int SH = TprShape<LHMAX, true, RM>::share, NG = NW / SH;   // groups of SH waves, one receiver each
+  __shared__ __align__(16) float sG[NG][NPAIR * 16];   // [pair][channel]
+  __shared__ int s_cnt[NG];
   const int ct = blockIdx.y;
   load_w3_bwd<P, RM, 64 * NW>(W3, K, ct, sW);
+  if (threadIdx.x < NG) s_cnt[threadIdx.x] = 0;
   __syncthreads();
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int g = l >> 4, kk = l & 15;
   const int kb = 16 * ct + 4 * g;   // the lane's four channels
-  float* sg = sG[w];
+  const int wg = w / SH, ws = w % SH;   // the wave's group, and its number there
+  float* sg = sG[wg];
+  int due = 0;
   float* dYc = dYp + (size_t)ct * E * 16;
-  const int stride = gridDim.x * NW;
-  // The next tile's edge, sender and radial operands are requested before a
-  // tile's last contraction; after a receiver's last tile they are those of the
-  // first tile of the wave's next receiver (`ready`), in flight while its G
-  // table is formed. (Conditional loads or stores in the middle of a tile would
+  // The next tile's edge and sender index are requested before a tile's last
+  // contraction. (Conditional loads or stores in the middle of a tile would
   // split it into basic blocks, and the compiler then moves the dY sums to the
   // last one, keeping the G table in registers: it spilled 1.3 to 2.8 KB.)
-  bool ready = false;
   int e = 0, src = 0;
-  RadOp<RM, RM == 1 ? 1 : 3> a;
-  RadOp<RM, RM == 1 ? 2 : 3> t;
   auto fetch = [&](int edge) {
     e = edge;
     src = snd[e];
     if constexpr (FIRST) src = src_map[src];
-    a.load(a3, e, g);
-    t.load(t3, e, g);
   };
-  for (int i = blockIdx.x * NW + w; i < N; i += stride) {
+  for (int i = blockIdx.x * NG + wg; i < N; i += gridDim.x * NG) {
     const int e_beg = rcv_off[i], e_end = rcv_off[i + 1];
-    if (e_beg == e_end) {
-      ready = false;
-      continue;
-    }
-    int nb = 0, ne = 0;   // the wave's next receiver's edges
-    if (i + stride < N) {
-      nb = rcv_off[i + stride];
-      ne = rcv_off[i + stride + 1];
-    }
-    if (!ready) fetch(min(e_beg + kk, e_end - 1));
-    __builtin_amdgcn_wave_barrier();   // the previous receiver's reads come first
-    build_g<LHMAX>(dAt + (size_t)i * MID * K + 16 * ct, K, inv_c, sg);
-    __builtin_amdgcn_wave_barrier();
-    for (int e0 = e_beg; e0 < e_end; e0 += 16) {
-      // the edge to fetch next (after the wave's last tile: this tile's, unused)
-      int e_next = e0 + 16 < e_end ? min(e0 + 16 + kk, e_end - 1) : (nb < ne ? min(nb + kk, ne - 1) : e);
+    if (e_beg == e_end) continue;
+    fetch(min(e_beg + 16 * ws + kk, e_end - 1));   // in flight while the G table is formed
+    group_sync<SH>(&s_cnt[wg], due);   // the previous receiver's reads come first
+    build_g<LHMAX, SH>(dAt + (size_t)i * MID * K + 16 * ct, K, inv_c, ws, sg);
+    group_sync<SH>(&s_cnt[wg], due);
+    for (int e0 = e_beg + 16 * ws; e0 < e_end; e0 += 16 * SH) {
+      int e_next = min(e0 + 16 * SH + kk, e_end - 1);   // (after the last tile: unused)
       // an offset of zero the compiler cannot see through: W3's operands and the
       // G table are read per tile, not held in registers across tiles
       int z0 = 0;
       __asm__ volatile("" : "+v"(z0), "+v"(e_next)::"memory");
       const int ec = e;
-      f4 hv[DIN], y4[4];
-      el_load_hy<DIN>(hv, y4, src, e, kb, h, Y, K);
+      RadOp<RM, RM == 1 ? 1 : 3> a;
+      RadOp<RM, RM == 1 ? 2 : 3> t;
+      a.load(a3, e, g);
+      t.load(t3, e, g);
+      const float* hrow = h + (size_t)src * DIN * K + kb;
+      f4 y4[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) y4[v] = reinterpret_cast<const f4*>(Y + (size_t)e * 16)[v];
       float y[16], dy[16];
 #pragma unroll
       for (int m = 0; m < 16; ++m) {
@@ -741,11 +755,13 @@ tpr_bwd_kernel(
       static_for<0, LHMAX + 1>([&](auto LHI) {
         constexpr int LH = decltype(LHI)::value;
         constexpr int PA = LH == 0 ? 0 : path_count(LH - 1), PB = path_count(LH);
-        f4 r[PB - PA], rp[PB - PA], dh[2 * LH + 1];
+        f4 r[PB - PA], rp[PB - PA], hv[2 * LH + 1], dh[2 * LH + 1];
+#pragma unroll
+        for (int m = 0; m < 2 * LH + 1; ++m) hv[m] = *reinterpret_cast<const f4*>(hrow + (LH * LH + m) * K);
         radial_group<PA, PB, P, RM>(sW + z0, a, t, r, rp);
-        if constexpr (RND) round_tile<PB - PA>(r, rnd);
+        if constexpr (RND != 0) round_tile<PB - PA>(r, RND);
         if constexpr (LH == LHMAX) {
-          fetch(e_next);   // the radial operands are spent
+          fetch(e_next);
         }
 #pragma unroll
         for (int m = 0; m < 2 * LH + 1; ++m) dh[m] = f4{0.f, 0.f, 0.f, 0.f};
@@ -764,7 +780,7 @@ tpr_bwd_kernel(
 #pragma unroll
           for (int m = 0; m < 2 * LH + 1; ++m) {
             Dm[m] = f4{0.f, 0.f, 0.f, 0.f};
-            Rh[m] = rv * hv[LH * LH + m];
+            Rh[m] = rv * hv[m];
           }
           mt::CG<LH, ly, T::lo>::each_pair([&](int m1, int m2, int pi) {
             const int gi = goff + pi;   // a constant after inlining
@@ -784,7 +800,7 @@ tpr_bwd_kernel(
           f4 d = f4{0.f, 0.f, 0.f, 0.f};   // dE/dR
 #pragma unroll
           for (int m = 0; m < 2 * LH + 1; ++m) {
-            d += hv[LH * LH + m] * Dm[m];
+            d += hv[m] * Dm[m];
             dh[m] += rv * Dm[m];
           }
           float s = dy[0];
@@ -818,7 +834,6 @@ tpr_bwd_kernel(
       }
       *reinterpret_cast<f4*>(dYc + (size_t)ec * 16 + 4 * g) = f4{dy[0], dy[1], dy[2], dy[3]};
     }
-    ready = nb < ne;
   }
 }
 
@@ -854,18 +869,23 @@ void tpr_bwd_launch(hipStream_t s, int N, int K, int E, const int* rcv_off, cons
                     const float* dAt, float* dYp, float* Q, int rnd) {
   using S = TprShape<LH, true, RM>;
   const int n_ct = K / 16;
-  dim3 grid(tpr_grid_x(N, n_ct, S::waves, S::blocks_per_cu), n_ct);
-  auto go = [&](auto R, auto F) {
-    tpr_bwd_kernel<LH, RM, decltype(R)::value, decltype(F)::value><<<grid, 64 * S::waves, 0, s>>>(
-        N, K, E, rcv_off, snd, src_map, a3, t3, W3, Y, h, inv_c, dAt, dYp, Q, rnd);
+  dim3 grid(tpr_grid_x(N, n_ct, S::waves / S::share, S::blocks_per_cu), n_ct);
+  auto go = [&](auto F) {
+    auto run = [&](auto R) {
+      tpr_bwd_kernel<LH, RM, decltype(R)::value, decltype(F)::value><<<grid, 64 * S::waves, 0, s>>>(
+          N, K, E, rcv_off, snd, src_map, a3, t3, W3, Y, h, inv_c, dAt, dYp, Q);
+    };
+    if (rnd == 1) run(std::integral_constant<int, 1>{});
+    else if (rnd == 2) run(std::integral_constant<int, 2>{});
+    else run(std::integral_constant<int, 0>{});
   };
   if constexpr (LH == 0) {
     if (!Q) {
-      rnd ? go(std::true_type{}, std::true_type{}) : go(std::false_type{}, std::true_type{});
+      go(std::true_type{});
       return;
     }
   }
-  rnd ? go(std::true_type{}, std::false_type{}) : go(std::false_type{}, std::false_type{});
+  go(std::false_type{});
 }
 }  // namespace
 
