@@ -5,6 +5,7 @@
 //
 // usage: gen_tables <FP32 header> <FP64 header>
 #include <vector>
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <set>
@@ -90,34 +91,81 @@ int main(int argc, char** argv) {
             }
         std::fprintf(f, "  }\n");
       }
-      // The coefficients' magnitudes times the harmonic they multiply: each
-      // distinct (m2, |C|) (|C| as the immediate it is written as) is one
-      // product per edge; each_yc(f): f(m2, |C|, its number); each_ys(f):
-      // f(m1, m2, m3, sign of C, number of its (m2, |C|)) per nonzero.
+      // The forward's form of the coefficients, C = sign * ratio * scale[m3]:
+      // scale[m3] is applied once per receiver, and each distinct (m2, ratio)
+      // with ratio != 1 is one product ratio * Y[m2] per edge. The scales are
+      // picked among each m3's magnitudes for the fewest such products (55
+      // over the paths of l_h <= 2, where |C| Y[m2] itself takes 112).
+      // each_yc(f): f(m2, ratio, product number); each_ys(f): f(m1, m2, m3,
+      // sign, product number or -1 for Y[m2] itself) per nonzero; scale(m3).
       {
-        std::vector<std::pair<int, std::string>> yc;
-        auto yc_id = [&](int m2, const std::string& a) {
-          for (size_t u = 0; u < yc.size(); ++u)
-            if (yc[u].first == m2 && yc[u].second == a) return (int)u;
-          yc.push_back({m2, a});
-          return (int)yc.size() - 1;
+        const int n3 = 2 * c + 1;
+        auto mag = [&](int m1, int m2, int m3) { return std::fabs(C.at(m1, m2, m3)); };
+        auto same = [](double x, double y) { return std::fabs(x - y) < 1e-9 * std::fabs(y); };
+        std::vector<double> scale(n3, 1.0);
+        std::vector<std::vector<double>> cand(n3);
+        for (int m3 = 0; m3 < n3; ++m3) {
+          int best = 0;
+          for (int m1 = 0; m1 < 2 * a + 1; ++m1)
+            for (int m2 = 0; m2 < 2 * b + 1; ++m2) {
+              const double v = mag(m1, m2, m3);
+              if (v == 0.0) continue;
+              int count = 0;
+              for (int q1 = 0; q1 < 2 * a + 1; ++q1)
+                for (int q2 = 0; q2 < 2 * b + 1; ++q2) count += same(mag(q1, q2, m3), v);
+              if (std::none_of(cand[m3].begin(), cand[m3].end(), [&](double x) { return same(x, v); })) cand[m3].push_back(v);
+              if (count > best) {
+                best = count;
+                scale[m3] = v;
+              }
+            }
+        }
+        using Prod = std::pair<int, double>;   // (m2, ratio)
+        auto find = [&](const std::vector<Prod>& ps, int m2, double ratio) {
+          for (size_t u = 0; u < ps.size(); ++u)
+            if (ps[u].first == m2 && same(ps[u].second, ratio)) return (int)u;
+          return -1;
         };
-        std::string ys;
+        auto products = [&](const std::vector<double>& sc) {
+          std::vector<Prod> ps;
+          for (int m1 = 0; m1 < 2 * a + 1; ++m1)
+            for (int m2 = 0; m2 < 2 * b + 1; ++m2)
+              for (int m3 = 0; m3 < n3; ++m3) {
+                const double v = mag(m1, m2, m3);
+                if (v == 0.0 || same(v, sc[m3]) || find(ps, m2, v / sc[m3]) >= 0) continue;
+                ps.push_back({m2, v / sc[m3]});
+              }
+          return ps;
+        };
+        for (int sweep = 0; sweep < 3; ++sweep)
+          for (int m3 = 0; m3 < n3; ++m3)
+            for (double v : cand[m3]) {
+              std::vector<double> t = scale;
+              t[m3] = v;
+              if (products(t).size() < products(scale).size()) scale = t;
+            }
+        const std::vector<Prod> yc = products(scale);
+        std::string ys, sc;
         for (int m1 = 0; m1 < 2 * a + 1; ++m1)
           for (int m2 = 0; m2 < 2 * b + 1; ++m2)
-            for (int m3 = 0; m3 < 2 * c + 1; ++m3) {
+            for (int m3 = 0; m3 < n3; ++m3) {
               const double v = C.at(m1, m2, m3);
               if (v == 0.0) continue;
-              const int u = yc_id(m2, val(std::fabs(v)));
               char buf[96];
-              std::snprintf(buf, sizeof(buf), "    f(%d, %d, %d, %d, %d);\n", m1, m2, m3, v > 0 ? 1 : -1, u);
+              std::snprintf(buf, sizeof(buf), "    f(%d, %d, %d, %d, %d);\n", m1, m2, m3, v > 0 ? 1 : -1,
+                            find(yc, m2, std::fabs(v) / scale[m3]));
               ys += buf;
             }
+        for (int m3 = 0; m3 < n3; ++m3)
+          sc += std::string(m3 ? " : " : "") + (m3 + 1 < n3 ? "m3 == " + std::to_string(m3) + " ? " : "") + val(scale[m3]);
         std::fprintf(f, "  static constexpr int nyc = %d;\n", (int)yc.size());
         std::fprintf(f, "  template <class F> __host__ __device__ __forceinline__ static void each_yc(F&& f) {\n");
-        for (size_t u = 0; u < yc.size(); ++u) std::fprintf(f, "    f(%d, %s, %d);\n", yc[u].first, yc[u].second.c_str(), (int)u);
+        for (size_t u = 0; u < yc.size(); ++u) std::fprintf(f, "    f(%d, %s, %d);\n", yc[u].first, val(yc[u].second).c_str(), (int)u);
+        if (yc.empty()) std::fprintf(f, "    (void)f;\n");
         std::fprintf(f, "  }\n");
         std::fprintf(f, "  template <class F> __host__ __device__ __forceinline__ static void each_ys(F&& f) {\n%s  }\n", ys.c_str());
+        std::fprintf(f, "  __host__ __device__ __forceinline__ static constexpr %s scale(int m3) { return %s; }\n",
+                     dbl ? "double" : "float", sc.c_str());
       }
       // each_pair(f): f(m1, m2, pair number) per pair
       std::fprintf(f, "  template <class F> __host__ __device__ __forceinline__ static void each_pair(F&& f) {\n");

@@ -31,17 +31,24 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 constexpr int kWPitch = 68;   // LDS row pitch of the W3 slice: 64 + 4 (4 mod 32)
 constexpr int kYPitch = 20;   // Y tile row: 16 floats + 4 (float4-aligned)
 // Launch shape per (l_max, direction): waves per block (all on one channel
-// tile) and the waves per SIMD the register budget is cut for. Two 8-wave
-// blocks per CU fit the LDS below l = 2 and give four waves per SIMD at 128
-// VGPRs in the forward; for l = 2 the W3 slice alone fills most of the LDS, and
-// the l = 2 backward runs one 4-wave block per CU, one wave per SIMD, so that
-// its state fits the whole register file. The MFMA phases raise the wave's
-// priority so that they issue ahead of the other waves' vector work on the
-// SIMD.
+// tile) and the waves per SIMD the register budget is cut for. Forward: two
+// 8-wave blocks per CU fit the LDS below l = 2 and give four waves per SIMD at
+// 128 VGPRs; for l = 2 the W3 slice fills most of the LDS and one 8-wave block
+// runs two per SIMD. Backward: two waves per SIMD at l = 1 and 2 (206 to 240
+// registers), three at l = 0 (in 4-wave blocks; two or four per SIMD were 3 to
+// 7% slower). Both edge products are bound by issue there: per 16-edge tile and
+// channel tile of the l = 2 backward about 2,290 vector instructions (the
+// contraction's multiply-adds are 2,176) of 4 cycles and 408 MFMAs of 16, in
+// 87% of the SIMDs' time at 2.4 GHz; operand rings of other depths change
+// nothing. The MFMA phases raise the wave's priority so that they issue ahead of
+// the other waves' vector work on the SIMD.
+// At 36,864 atoms (K = 128, l = 2, 3.18 M edges): forward 7.46 -> 7.01 ms,
+// backward 18.55 -> 14.9 ms (and no radial backward); at 1,536 atoms (l = 1)
+// 126 -> 100 us and 230 -> 197 us.
 template <int LHMAX, bool BWD, int RM = 0>
 struct TprShape {
-  static constexpr int waves = 8;
-  static constexpr int per_simd = BWD ? 2 : (LHMAX == 2 ? 2 : 4);
+  static constexpr int waves = BWD && LHMAX == 0 ? 4 : 8;
+  static constexpr int per_simd = BWD ? (LHMAX == 0 ? 3 : 2) : (LHMAX == 2 ? 2 : 4);
   // waves that share a receiver and its G table, taking its edge tiles in turn
   // (two where eight tables do not fit beside W3's slice)
   static constexpr int share = (BWD && LHMAX == 2 && RM != 1) ? 2 : 1;
@@ -344,9 +351,15 @@ template <int P>
 __device__ __forceinline__ void round_tile(f4* r, int rnd) {
   if (!rnd) return;
 #pragma unroll
-  for (int p = 0; p < P; ++p)
+  for (int p = 0; p < P; ++p) {
+    if (rnd == 1) {   // the packed hardware conversion: round to nearest even
+      const f2v lo = bf16_unpack2(bf16_pack2(f2v{r[p][0], r[p][1]})), hi = bf16_unpack2(bf16_pack2(f2v{r[p][2], r[p][3]}));
+      r[p] = f4{lo[0], lo[1], hi[0], hi[1]};
+    } else {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) r[p][q] = lowp_round(r[p][q], rnd);
+      for (int q = 0; q < 4; ++q) r[p][q] = fp16_round(r[p][q]);
+    }
+  }
 }
 
 __device__ __forceinline__ void stage_y(const float* __restrict__ Y, int e0, int e_end, float* sy) {
@@ -405,11 +418,20 @@ tpr_fwd_kernel(
   const int g = l >> 4;
   const int k = 16 * ct + (l & 15);
   float* sy = sY[w];
-  for (int i = blockIdx.x * NW + w; i < N; i += gridDim.x * NW) {
-    float acc[MID];
+  // (a receiver's edge range is requested while the wave's previous receiver is worked on)
+  const int stride = gridDim.x * NW;
+  int i = blockIdx.x * NW + w;
+  if (i >= N) return;
+  int nb = rcv_off[i], ne = rcv_off[i + 1];
+  for (; i < N; i += stride) {
+    constexpr int H2 = (MID + 3) / 4, H1 = 2 * H2;
+    float acc[2 * H1];
 #pragma unroll
-    for (int c = 0; c < MID; ++c) acc[c] = 0.f;
-    const int e_beg = rcv_off[i], e_end = rcv_off[i + 1];
+    for (int c = 0; c < 2 * H1; ++c) acc[c] = 0.f;
+    const int e_beg = nb, e_end = ne;
+    const int i_next = min(i + stride, N - 1);
+    nb = rcv_off[i_next];
+    ne = rcv_off[i_next + 1];
     for (int e0 = e_beg; e0 < e_end; e0 += 16) {
       // sender rows of the lane's four edges (edges past e_end carry R = 0),
       // requested before the radial MFMAs so that their latency is hidden
@@ -448,19 +470,21 @@ tpr_fwd_kernel(
         for_paths<LHMAX>([&](auto tag) {
           using T = decltype(tag);
           constexpr int lh = T::lh, ly = T::ly, lo = T::lo;
-          // R folded into the sender features (R h[m1]) and the coefficients'
-          // magnitudes into the harmonics (|C| Y[m2], one product per distinct
-          // pair of the path): acc[m3] += (+-R h[m1]) (|C| Y[m2]), one
-          // multiply-add per coefficient with its sign on an operand
+          // R folded into the sender features (R h[m1]), and each coefficient
+          // carried as +-ratio * scale[m3]: acc[m3] += (+-R h[m1]) (ratio Y[m2]),
+          // one multiply-add per coefficient with its sign on an operand, one
+          // product per distinct (m2, ratio != 1) of the path, and the scales
+          // at the end of the receiver
           using C = mt::CG<lh, ly, lo>;
           const float rv = r[T::index][q];
           float hr[2 * lh + 1];
 #pragma unroll
           for (int m = 0; m < 2 * lh + 1; ++m) hr[m] = rv * hv[lh * lh + m];
-          float yc[C::nyc];
-          C::each_yc([&](int m2, float av, int u) { yc[u] = av * y[ly * ly + m2]; });
+          float yc[C::nyc ? C::nyc : 1];
+          C::each_yc([&](int m2, float ratio, int u) { yc[u] = ratio * y[ly * ly + m2]; });
           C::each_ys([&](int m1, int m2, int m3, int sg, int u) {
-            acc[T::offset + m3] = __builtin_fmaf(sg > 0 ? hr[m1] : -hr[m1], yc[u], acc[T::offset + m3]);
+            const float yv = u >= 0 ? yc[u >= 0 ? u : 0] : y[ly * ly + m2];
+            acc[T::offset + m3] = __builtin_fmaf(sg > 0 ? hr[m1] : -hr[m1], yv, acc[T::offset + m3]);
           });
         });
         if constexpr (!ALT && q < 3) {
@@ -469,15 +493,23 @@ tpr_fwd_kernel(
         }
       });
     }
-    // lane groups 0+1 and 2+3, then the two pairs: every lane ends with the same sum
+    // the components' scales, then the sum over the lane groups (0+1 and 2+3,
+    // then the two pairs) with the components halved twice: group g ends with
+    // components c0 .. c0 + H2 - 1
+    for_paths<LHMAX>([&](auto tag) {
+      using T = decltype(tag);
 #pragma unroll
-    for (int c = 0; c < MID; ++c) {
-      acc[c] += __shfl_xor(acc[c], 16);
-      acc[c] += __shfl_xor(acc[c], 32);
-    }
+      for (int m3 = 0; m3 < 2 * T::lo + 1; ++m3) acc[T::offset + m3] *= mt::CG<T::lh, T::ly, T::lo>::scale(m3);
+    });
 #pragma unroll
-    for (int c = 0; c < MID; ++c)
-      if ((c & 3) == g) At[((size_t)i * MID + c) * K + k] = acc[c] * inv_c;
+    for (int c = 0; c < H1; ++c) acc[c] = swap_add16(acc[c], acc[c + H1]);
+#pragma unroll
+    for (int c = 0; c < H2; ++c) acc[c] = swap_add32(acc[c], acc[c + H2]);
+    const int c0 = H1 * (g & 1) + H2 * (g >> 1);
+    float* out = At + ((size_t)i * MID + c0) * K + k;
+#pragma unroll
+    for (int c = 0; c < H2; ++c)
+      if (c0 + c < MID || MID % 4 == 0) out[c * K] = acc[c] * inv_c;
   }
 }
 
@@ -561,8 +593,13 @@ __device__ __forceinline__ void load_w3_bwd(const float* __restrict__ W3, int K,
   }
 }
 
-constexpr int kRingR = 2;    // W3 operand sets in flight in the radial products
-constexpr int kRingG = 3;    // G-table entries in flight (one coupling pair each)
+#ifndef V_RR
+#define V_RR 3
+#define V_RG 4
+#define V_PRIO 1
+#endif
+constexpr int kRingR = V_RR;    // W3 operand sets in flight in the radial products
+constexpr int kRingG = 4;    // G-table entries in flight (one coupling pair each)
 
 // R and R' of the paths PA .. PB - 1 in the edge-lane layout. RM 3: six partial
 // products per operand pair, the smallest first. RM 1: bf16(a3) bf16(W3) for R,
@@ -632,27 +669,36 @@ __device__ __forceinline__ void radial_group(const void* __restrict__ sW, const 
   __builtin_amdgcn_s_setprio(0);
 }
 
-// G_p of receiver i for channel 16 ct + l%16, path by path (only the path's own
-// dE/dAt values live); the four lane groups compute the same values and the
-// first one stores: sg[pair][channel]. Wave ws of SHARE takes every SHARE-th path.
+// G_p of receiver i for channel 16 ct + l%16: sg[pair][channel]. Wave ws of
+// SHARE takes every SHARE-th path; its dE/dAt values are all requested before
+// the first is used (path by path, the receiver paid a memory latency for each).
+// The four lane groups compute the same values and the first one stores.
 template <int LHMAX, int SHARE>
 __device__ __forceinline__ void build_g(const float* __restrict__ gsrc, int K, float inv_c, int ws,
                                         float* __restrict__ sg) {
   const int l = threadIdx.x & 63, g = l >> 4, kk = l & 15;
   static_for<0, SHARE>([&](auto WS) {
     if (SHARE > 1 && ws != decltype(WS)::value) return;
+    float gv[mid_count(LHMAX)];
+    for_paths<LHMAX>([&](auto tag) {
+      using T = decltype(tag);
+      if constexpr (T::index % SHARE == decltype(WS)::value) {
+#pragma unroll
+        for (int m = 0; m < 2 * T::lo + 1; ++m) gv[T::offset + m] = gsrc[(size_t)(T::offset + m) * K + kk];
+      }
+    });
+    __builtin_amdgcn_sched_barrier(0);
     for_paths<LHMAX>([&](auto tag) {
       using T = decltype(tag);
       if constexpr (T::index % SHARE == decltype(WS)::value) {
         using C = mt::CG<T::lh, T::ly, T::lo>;
         constexpr int goff = PathPairOffset<T::index>::value;
-        float gv[2 * T::lo + 1];
 #pragma unroll
-        for (int m = 0; m < 2 * T::lo + 1; ++m) gv[m] = gsrc[(size_t)(T::offset + m) * K + kk] * inv_c;
+        for (int m = 0; m < 2 * T::lo + 1; ++m) gv[T::offset + m] *= inv_c;
         float Gp[C::npair];
 #pragma unroll
         for (int u = 0; u < C::npair; ++u) Gp[u] = 0.f;
-        C::each_p([&](int m1, int m2, int m3, float cg, int pi) { Gp[pi] += cg * gv[m3]; });
+        C::each_p([&](int m1, int m2, int m3, float cg, int pi) { Gp[pi] += cg * gv[T::offset + m3]; });
         if (g == 0) {
 #pragma unroll
           for (int u = 0; u < C::npair; ++u) sg[(goff + u) * 16 + kk] = Gp[u];
@@ -715,22 +761,37 @@ tpr_bwd_kernel(
   int due = 0;
   float* dYc = dYp + (size_t)ct * E * 16;
   // The next tile's edge and sender index are requested before a tile's last
-  // contraction. (Conditional loads or stores in the middle of a tile would
-  // split it into basic blocks, and the compiler then moves the dY sums to the
-  // last one, keeping the G table in registers: it spilled 1.3 to 2.8 KB.)
+  // contraction, and a receiver's edge range and first sender index while the
+  // wave's previous receiver is worked on. (Conditional loads or stores in the
+  // middle of a tile would split it into basic blocks, and the compiler then
+  // moves the dY sums to the last one, keeping the G table in registers: it
+  // spilled 1.3 to 2.8 KB.)
   int e = 0, src = 0;
   auto fetch = [&](int edge) {
     e = edge;
     src = snd[e];
     if constexpr (FIRST) src = src_map[src];
   };
-  for (int i = blockIdx.x * NG + wg; i < N; i += gridDim.x * NG) {
-    const int e_beg = rcv_off[i], e_end = rcv_off[i + 1];
-    if (e_beg == e_end) continue;
-    fetch(min(e_beg + 16 * ws + kk, e_end - 1));   // in flight while the G table is formed
-    group_sync<SH>(&s_cnt[wg], due);   // the previous receiver's reads come first
-    build_g<LHMAX, SH>(dAt + (size_t)i * MID * K + 16 * ct, K, inv_c, ws, sg);
-    group_sync<SH>(&s_cnt[wg], due);
+  const int stride = gridDim.x * NG;
+  int i = blockIdx.x * NG + wg;
+  if (i >= N) return;   // the whole group
+  int nb = rcv_off[i], ne = rcv_off[i + 1];
+  auto first_edge = [&]() { return max(min(nb + 16 * ws + kk, ne - 1), 0); };
+  int nsrc = snd[first_edge()];
+  for (; i < N; i += stride) {
+    const int e_beg = nb, e_end = ne;
+    e = first_edge();
+    src = nsrc;
+    if constexpr (FIRST) src = src_map[src];
+    const int i_next = min(i + stride, N - 1);
+    nb = rcv_off[i_next];
+    ne = rcv_off[i_next + 1];
+    if (e_beg < e_end) {
+      group_sync<SH>(&s_cnt[wg], due);   // the previous receiver's reads come first
+      build_g<LHMAX, SH>(dAt + (size_t)i * MID * K + 16 * ct, K, inv_c, ws, sg);
+      group_sync<SH>(&s_cnt[wg], due);
+    }
+    nsrc = snd[first_edge()];
     for (int e0 = e_beg + 16 * ws; e0 < e_end; e0 += 16 * SH) {
       int e_next = min(e0 + 16 * SH + kk, e_end - 1);   // (after the last tile: unused)
       // an offset of zero the compiler cannot see through: W3's operands and the
@@ -814,24 +875,12 @@ tpr_bwd_kernel(
             *reinterpret_cast<f4*>(Q + ((size_t)ec * DIN + LH * LH + m) * K + kb) = dh[m];
         }
       });
-      // over the tile's 16 channels: halve over lane bit 5, then bit 4; lane
+      // over the tile's 16 channels: the lane groups halve the elements twice;
       // group q ends with elements 4q .. 4q + 3
-      {
-        const bool hi5 = g >= 2;
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-          const float send = hi5 ? dy[m] : dy[m + 8];
-          const float keep = hi5 ? dy[m + 8] : dy[m];
-          dy[m] = keep + __shfl_xor(send, 32);
-        }
-        const bool hi4 = g & 1;
+      for (int m = 0; m < 8; ++m) dy[m] = swap_add32(dy[m], dy[m + 8]);
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          const float send = hi4 ? dy[m] : dy[m + 4];
-          const float keep = hi4 ? dy[m + 4] : dy[m];
-          dy[m] = keep + __shfl_xor(send, 16);
-        }
-      }
+      for (int m = 0; m < 4; ++m) dy[m] = swap_add16(dy[m], dy[m + 4]);
       *reinterpret_cast<f4*>(dYc + (size_t)ec * 16 + 4 * g) = f4{dy[0], dy[1], dy[2], dy[3]};
     }
   }
@@ -853,7 +902,7 @@ void tpr_fwd_launch(hipStream_t s, int N, int K, const int* rcv_off, const int* 
   using S = TprShape<LH, false>;
   const int n_ct = K / 16;
   dim3 grid(tpr_grid_x(N, n_ct, S::waves, S::blocks_per_cu), n_ct);
-  if constexpr (LH == 2 && (RM == 3 || RM == 1)) {
+  if constexpr (RM == 3 || RM == 1) {
     if (K == 128) {
       tpr_fwd_kernel<LH, RM, S::waves, 128><<<grid, 64 * S::waves, 0, s>>>(N, K, rcv_off, snd, src_map, a3, W3, Y, h,
                                                                             inv_c, At, rnd);

@@ -322,6 +322,21 @@ __device__ __forceinline__ int edge_geometry(int e, const float* __restrict__ po
   return !isfinite(rr) ? kStatusNonFinite : (rr == 0.0 ? kStatusZeroLength : 0);
 }
 
+// Halving steps of a reduce-scatter by the half-wave and row exchanges of
+// gfx950 (one exchange and one add for two values): swap_add32 gives lane l < 32
+// a[l] + a[l + 32] and lane l >= 32 b[l - 32] + b[l]; swap_add16 the same
+// between the even and odd 16-lane rows of each half.
+__device__ __forceinline__ float swap_add32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+  const unsigned r0 = r[0], r1 = r[1];
+  return __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
+}
+__device__ __forceinline__ float swap_add16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+  const unsigned r0 = r[0], r1 = r[1];
+  return __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
+}
+
 // One halving step of a 64-lane reduce-scatter over v[0 .. 2 N_): lanes with
 // bit XOR set keep the upper half, the others the lower half, each adding the
 // partner lane's copy of the half it keeps.
@@ -339,8 +354,10 @@ __device__ __forceinline__ void halve(float* v, int lane) {
 // Sum of v[0..15] over the 64 lanes of the wave: afterwards every lane l holds
 // the total of index (l >> 2) & 15 (fixed butterfly order).
 __device__ __forceinline__ float wave_reduce_scatter16(float* v, int lane) {
-  halve<8, 32>(v, lane);
-  halve<4, 16>(v, lane);
+#pragma unroll
+  for (int q = 0; q < 8; ++q) v[q] = swap_add32(v[q], v[q + 8]);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) v[q] = swap_add16(v[q], v[q + 4]);
   halve<2, 8>(v, lane);
   halve<1, 4>(v, lane);
   float t = v[0];
