@@ -231,8 +231,7 @@ mace_status mace_layer0_form(mace_graph* g, int32_t request, int32_t* in_use);
 
 /* Operands of the P*K-wide last radial layer (formed inside the edge-product
  * kernels of the layers in per-edge form) in the modes other than
- * MACE_BF16_RADIAL.  (The channel-mixing linears stay on FP32 MFMA: split
- * products were measured slower there, where the MFMA is not the bound.)
+ * MACE_BF16_RADIAL, and in MACE_FP32 of the channel-mixing linears too.
  *   MACE_PRODUCTS_FP32:       FP32 MFMA (v_mfma_f32_16x16x4_f32);
  *   MACE_PRODUCTS_SPLIT_BF16: every FP32 operand x carried as x0 + x1 + x2,
  *     the bfloat16 roundings of x, x - x0 and x - x0 - x1 (together exact),

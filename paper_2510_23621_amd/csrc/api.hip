@@ -52,6 +52,7 @@ struct Model {
   int l0_ki = 0;           // channels of the factorised first layer's U (64 S), 0 when S > kL0MaxSpecies
   int64_t l0_off = 0;      // after those: its weights [4][S][l0_ki][K] (transposed copy [4][S][K][l0_ki])
   int64_t total_ext = 0;   // blob + combined weights (FP32 copies only)
+  int64_t split_part() const { return (total_ext + 7) / 8 * 8; }   // elements of one part of the split copies
   int max_P = 0, max_mid = 0, max_din = 0, max_dout = 0;
 };
 
@@ -171,6 +172,7 @@ struct Buffers {
   float *w = nullptr, *wT = nullptr, *sp_table = nullptr, *sp_round = nullptr;   // (rounded copy: precision study)
   float* w_round = nullptr;   // precision study: rounded copies of the last radial layers' weights
   unsigned short *wbf = nullptr, *wbfT = nullptr;   // 16-bit K-packed copies (BF16- / FP16-linear modes)
+  unsigned short *wsp = nullptr, *wspT = nullptr;   // three bfloat16 parts of w and wT, K-packed (FP32 mode)
   int *species = nullptr, *snd = nullptr, *rcv = nullptr, *rcv_off = nullptr, *snd_off = nullptr,
       *snd_perm = nullptr, *graph_off = nullptr, *quad_node = nullptr, *quad_species = nullptr,
       *quad_node8 = nullptr, *quad_species8 = nullptr;
@@ -207,6 +209,8 @@ void carve(const Model& m, int64_t N, int64_t E, int G, Carver& c, Buffers& b) {
   b.wT = c.take<float>(m.total_ext);
   b.wbf = c.take<unsigned short>(m.total);
   b.wbfT = c.take<unsigned short>(m.total);
+  b.wsp = c.take<unsigned short>(3 * m.split_part());
+  b.wspT = c.take<unsigned short>(3 * m.split_part());
   b.sp_table = c.take<float>(S * K);
   b.sp_round = c.take<float>(S * K);
   b.w_round = c.take<float>(m.total_ext);
@@ -650,6 +654,10 @@ LinArgs largs(mace_graph* h, const float* x, float* y, const float* residual, bo
   a.w = transposed ? h->b.wT : h->b.w;
   a.wt = transposed ? h->b.w : h->b.wT;
   a.wbf = transposed ? h->b.wbfT : h->b.wbf;
+  // split products in the FP32 mode (the packed blocks are read in 16-byte pieces)
+  const bool split = h->prec == MACE_FP32 && h->radial_split && h->m.comb_off % 8 == 0;
+  a.wsp = split ? (transposed ? h->b.wspT : h->b.wsp) : nullptr;
+  a.wsp_part = h->m.split_part();
   a.quad_node = h->b.quad_node;
   a.quad_species = h->b.quad_species;
   a.n_quads = h->n_quads;
@@ -1436,6 +1444,19 @@ mace_status mace_graph_setup(const mace_model_desc* desc, const float* weights, 
   chk(hipMemsetAsync(b.status, 0, sizeof(int), s));
   launch_species_table(s, (int)S, (int)K, b.w + m.off.at("embed"), b.w + m.off.at("0.up.0"),
                        lowp_mode(prec), b.sp_table);
+  if (prec == MACE_FP32) {
+    // split packed copies of every K x K block, of the composed layer-0 weights
+    // and of the factorised first layer's, and of their transposes
+    auto pack = [&](int KI, int KO, int64_t blocks, int64_t off) {
+      launch_pack_split(s, KI, KO, blocks, m.split_part(), b.w + off, b.wsp + off);
+      launch_pack_split(s, KO, KI, blocks, m.split_part(), b.wT + off, b.wspT + off);
+    };
+    for (auto& t : m.tensors)
+      if (t.shape.size() >= 2 && t.shape[t.shape.size() - 1] == K && t.shape[t.shape.size() - 2] == K)
+        pack((int)K, (int)K, t.size() / (K * K), t.offset);
+    pack((int)K, (int)K, 4 * S, m.comb_off);
+    if (m.l0_ki) pack(m.l0_ki, (int)K, 4 * S, m.l0_off);
+  }
   if (prec == MACE_FP64) f64_widen(s, (size_t)m.total, b.w, h->b64.w);
   chk(hipGetLastError());
   chk(hipStreamSynchronize(s));  // host vectors go out of scope below

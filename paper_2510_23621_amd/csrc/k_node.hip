@@ -48,11 +48,18 @@ __device__ __forceinline__ us8 lowp_bits8(f4 lo, f4 hi) {
 // Column tiles of 16 per block. Four by default (measured at 1,536 and 36,864
 // atoms: 4 beats 2, most in the 16-bit modes); at K = 128 all eight when the
 // launch still has kLinWideGrid blocks, so that each input row is read by one
-// block only (36,864 atoms: FP32 linears 4.24 -> 3.64 ms per step; at 1,536
+// block only (36,864 atoms, FP32 products: 4.24 -> 3.64 ms per step; at 1,536
 // atoms, 384 blocks, eight was slower).
 constexpr int kLinCt = 4;
 constexpr int kLinCtWide = 8;
 constexpr int kLinWideGrid = 2048;
+// Split products from one block per CU on. Below it the FP32 kernel with a column
+// tile per block is the faster: it spreads a launch over K/16 times the blocks
+// and reads 4 bytes of weights per element in place of 6 (one molecule: 97
+// against 109 us of linears per step; at 1,536 atoms, whose
+// launches have 96 to 400 blocks, 141 us with the line at 256, 164 with none,
+// 169 at 400).
+constexpr int kLinSplitMinGrid = 256;
 constexpr int kLinSmallGrid = 512;   // blocks below which a square linear takes one column tile per block
 
 // LP: 0 FP32, 1 BF16, 2 FP16 (the 16-bit paths share everything but the
@@ -214,6 +221,173 @@ linear_kernel(const LinLaunch* __restrict__ Lp, LinArgs a) {
       y[o] = v;
     }
   }
+}
+
+// The FP32 linears on split-BF16 MFMA (FP32-accurate: every FP32 operand as
+// three bfloat16 parts, six partial products added from the smallest to the
+// largest, as in the edge products; 96 MFMA cycles per 16 x 16 x 32 block in
+// place of 256). The weights come split and packed ([KI/8][K][8] per part,
+// written once at setup). Operand roles: A = 16 weight columns, B = 16 rows, so
+// that a lane ends with four consecutive columns of one row. Bound by neither
+// the MFMA nor HBM alone: 36,864 atoms (l = 2, K = 128) 3.11 -> 1.88 ms per step
+// against FP32 products (59 % of the FP32 MFMA peak), 1,536 atoms 0.183 -> 0.141.
+__device__ __forceinline__ void split_mfma(f4 (&acc)[2], const us8 (&wv)[2][3], const us8 (&xb)[3]) {
+  constexpr int iw[6] = {0, 1, 2, 0, 1, 0}, ix[6] = {2, 1, 0, 1, 0, 0};
+#pragma unroll
+  for (int n = 0; n < 6; ++n)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, wv[j][iw[n]]),
+                                                       __builtin_bit_cast(bf8, xb[ix[n]]), acc[j], 0, 0, 0);
+}
+// weight columns n0 + 16 j + l%16, k = k0 + 8 (l/16) .. + 7, three parts
+__device__ __forceinline__ void split_weights(us8 (&wv)[2][3], const unsigned short* w, int64_t part, int K, int k0,
+                                              int n0, int l) {
+  const unsigned short* p = w + ((size_t)(k0 / 8 + (l >> 4)) * K + n0 + (l & 15)) * 8;
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) wv[j][q] = *reinterpret_cast<const us8*>(p + q * part + 16 * 8 * j);
+}
+
+// A block owns one quad (64 rows of one species), one output component and
+// 32 NCG columns; its waves are NCG column groups of 32 times 4/NCG row parts
+// (one at NCG = 3). The input rows go through LDS in k chunks of 32: each value
+// is split once, by the thread that loaded it, into three part planes that every
+// wave reads. Each weight operand is read from memory by the one wave of a row
+// part that uses it, so the weights need no LDS and no barrier. Chunks of 32:
+// 15.6 KB and 96 registers, so five waves per SIMD (chunks of 64: three, 5 %
+// slower); 128-row blocks read the weights half as often, without a gain.
+template <int NCG>
+__global__ void __launch_bounds__(NCG == 3 ? 192 : 256) __attribute__((amdgpu_waves_per_eu(4)))
+linear_split_kernel(const LinLaunch* __restrict__ Lp, LinArgs a, int KI) {
+  constexpr int W = NCG == 3 ? 3 : 4, RT = kLinQuad * NCG / W;   // waves, row tiles per wave
+  constexpr int ROWS = 16 * kLinQuad, NT = 64 * W, KC = 32;
+  constexpr int XN = ROWS * KC / 4, XU = (XN + NT - 1) / NT;     // float4 per chunk, per thread
+  constexpr int PP = KC + 8;   // plane row pitch (20 dwords: conflict-free 16-byte reads)
+  constexpr int PLANE = ROWS * PP;
+  __shared__ __align__(16) unsigned short sP[3 * PLANE];
+  __shared__ int s_node[ROWS];
+  const LinLaunch& L = *Lp;
+  const LinGC gcx = L.gc[blockIdx.y];
+  const LinGroup grp = L.plan.g[gcx.g];
+  const int c = gcx.c, K = a.K;
+  const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
+  const int n0 = 32 * (NCG * blockIdx.z + w % NCG), rp = w / NCG;
+  const int quad = blockIdx.x;
+  const int z = a.quad_species[quad];
+  if (tid < ROWS) s_node[tid] = a.quad_node[(size_t)quad * ROWS + tid];
+  __syncthreads();
+  int node[XU];   // the thread's part of a chunk: float4 f % 8 of row f / 8, f = tid + NT u
+#pragma unroll
+  for (int u = 0; u < XU; ++u) node[u] = s_node[min(tid + NT * u, XN - 1) / (KC / 4)];
+  f4 xv[XU];
+  auto load_rows = [&](int tm, int k0) {
+    const LinTerm& term = L.plan.t[tm];
+    const float* x = term.src ? a.x2 : a.x;
+    const int cin = term.src ? L.plan.cin2 : L.plan.cin;
+#pragma unroll
+    for (int u = 0; u < XU; ++u) {
+      const float keep = node[u] >= 0 ? 1.f : 0.f;   // a row without a node: node 0's, zeroed
+      const int f = min(tid + NT * u, XN - 1);
+      xv[u] = *reinterpret_cast<const f4*>(x + ((size_t)max(node[u], 0) * cin + term.in_c0 + c) * KI + k0 +
+                                           4 * (f % (KC / 4))) * keep;
+    }
+  };
+  f4 acc[RT][2];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) acc[rt][0] = acc[rt][1] = f4{0.f, 0.f, 0.f, 0.f};
+  int tm = grp.t0, k0 = 0;
+  if (tm < grp.t1) load_rows(tm, 0);
+  while (tm < grp.t1) {
+    us8 wv[2][3];
+    const LinTerm& term = L.plan.t[tm];
+    split_weights(wv, a.wsp + term.w_off + (term.species ? (int64_t)z * L.plan.w_sstride : 0), a.wsp_part, K, k0, n0, l);
+    __syncthreads();   // the previous chunk's planes have been read
+#pragma unroll
+    for (int u = 0; u < XU; ++u) {
+      const int f = tid + NT * u;
+      if (XN % NT && f >= XN) continue;
+      unsigned p0[2], p1[2], p2[2];
+      split3_pair(f2v{xv[u][0], xv[u][1]}, p0[0], p1[0], p2[0]);
+      split3_pair(f2v{xv[u][2], xv[u][3]}, p0[1], p1[1], p2[1]);
+      unsigned short* d = sP + f / (KC / 4) * PP + 4 * (f % (KC / 4));
+      *reinterpret_cast<uint2*>(d) = make_uint2(p0[0], p0[1]);
+      *reinterpret_cast<uint2*>(d + PLANE) = make_uint2(p1[0], p1[1]);
+      *reinterpret_cast<uint2*>(d + 2 * PLANE) = make_uint2(p2[0], p2[1]);
+    }
+    __syncthreads();
+    k0 += KC;
+    if (k0 >= KI) {
+      k0 = 0;
+      ++tm;
+    }
+    if (tm < grp.t1) load_rows(tm, k0);   // in flight during this chunk's MFMAs
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      const unsigned short* r = sP + (16 * (rp * RT + rt) + (l & 15)) * PP + 8 * (l >> 4);
+      us8 xb[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) xb[q] = *reinterpret_cast<const us8*>(r + q * PLANE);
+      split_mfma(acc[rt], wv, xb);
+    }
+  }
+  float* y = grp.dst ? a.y2 : a.y;
+  const int cout = grp.dst ? L.plan.cout2 : L.plan.cout;
+  const float* residual = grp.dst ? nullptr : a.residual;
+  const bool bias = a.bias0 && grp.out_c0 + c == 0 && !grp.dst;
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    const int out = s_node[16 * (rp * RT + rt) + (l & 15)];
+    if (out < 0) continue;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int col = n0 + 16 * j + 4 * (l >> 4);
+      const size_t o = ((size_t)out * cout + grp.out_c0 + c) * K + col;
+      f4 v = acc[rt][j];
+      if (residual) v += *reinterpret_cast<const f4*>(residual + o);
+      if (a.accumulate) v += *reinterpret_cast<const f4*>(y + o);
+      if (bias) v += *reinterpret_cast<const f4*>(a.bias0 + col);
+      *reinterpret_cast<f4*>(y + o) = v;
+    }
+  }
+}
+
+bool launch_linear_split(hipStream_t s, const LinPlanRef& P, const LinArgs& a, int KI) {
+  const int64_t qc = (int64_t)a.n_quads * P.host.n_gc;
+  // columns per block: all K up to 128, two halves of a factorised first layer's 192 or 256
+  const int nz = a.K > 128 ? 2 : 1, ncg = a.K / 32 / nz;
+  if (qc * nz < kLinSplitMinGrid) return false;
+  const dim3 grid(a.n_quads, P.host.n_gc, nz);
+  switch (ncg) {
+    case 1: linear_split_kernel<1><<<grid, 256, 0, s>>>(P.dev, a, KI); break;
+    case 2: linear_split_kernel<2><<<grid, 256, 0, s>>>(P.dev, a, KI); break;
+    case 3: linear_split_kernel<3><<<grid, 192, 0, s>>>(P.dev, a, KI); break;
+    case 4: linear_split_kernel<4><<<grid, 256, 0, s>>>(P.dev, a, KI); break;
+  }
+  return true;
+}
+
+// The split packed copy of nb consecutive KI x K blocks (row-major [in][out]) of
+// src: part q of element (k, n) of a block at q part + ((k/8) K + n) 8 + k%8 of it
+__global__ void pack_split_kernel(int KI, int K, int64_t n, int64_t part, const float* __restrict__ src,
+                                  unsigned short* __restrict__ dst) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int64_t blk = i / ((int64_t)KI * K), r = i % ((int64_t)KI * K);
+  const int k = (int)(r / K), col = (int)(r % K);
+  unsigned p0, p1, p2;
+  split3_pair(f2v{src[i], 0.f}, p0, p1, p2);
+  unsigned short* d = dst + blk * KI * K + ((size_t)(k / 8) * K + col) * 8 + k % 8;
+  d[0] = (unsigned short)p0;
+  d[part] = (unsigned short)p1;
+  d[2 * part] = (unsigned short)p2;
+}
+
+void launch_pack_split(hipStream_t s, int KI, int K, int64_t blocks, int64_t part, const float* src,
+                       unsigned short* dst) {
+  const int64_t n = blocks * KI * K;
+  if (n > 0) pack_split_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(KI, K, n, part, src, dst);
 }
 
 // Three linears in a row on one component, in one launch (the 16-bit modes'
@@ -398,6 +572,7 @@ void launch_linear(hipStream_t s, const LinPlanRef& P, const LinArgs& a) {
   const int halves = (a.K / 16 + kLinCt - 1) / kLinCt;
   dim3 grid(a.n_quads, P.host.n_gc, halves), block(64 * kLinQuad);
   const int KI0 = a.KI > 0 ? a.KI : a.K;
+  if (a.wsp && launch_linear_split(s, P, a, KI0)) return;
   if (a.K == 128 && KI0 <= 128 && (int64_t)a.n_quads * P.host.n_gc >= kLinWideGrid) {
     // wide blocks: all 128 output columns, each input row read once
     dim3 gw(a.n_quads, P.host.n_gc, 1);

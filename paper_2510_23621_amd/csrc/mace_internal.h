@@ -416,6 +416,8 @@ struct LinArgs {
   const float* w;           // weight base (FP32, row-major [in][out])
   const float* wt;          // the same blob with every K x K block transposed ([out][in])
   const unsigned short* wbf;  // same tensors in the low precision (bf16 or binary16 bits), each K x K block packed [K/8][K][8]
+  const unsigned short* wsp;  // FP32 modes: the blob's three bfloat16 parts, wsp_part apart, each block packed as in wbf
+  int64_t wsp_part;
   const int* quad_node;     // [n_quads][kLinQuad][16]: node of MFMA row r of wave w of a block, -1 for none
                             // (a block's nodes are up to kLinQuad tiles of 16 nodes of one species)
   const int* quad_species;  // [n_quads]
@@ -564,6 +566,8 @@ void launch_symcon_fwd(hipStream_t s, int lout_max, int N, int K, const int* spe
 void launch_symcon_bwd(hipStream_t s, int lout_max, int N, int K, const int* species, const float* A,
                        SymW w, const float* dB, float* dA, int rnd);
 void launch_linear(hipStream_t s, const LinPlanRef& plan, const LinArgs& a);
+void launch_pack_split(hipStream_t s, int KI, int K, int64_t blocks, int64_t part, const float* src,
+                       unsigned short* dst);
 // Algorithmic work of one linear launch over N nodes: flops = 2 K^2 per
 // (node, term component); bytes = every distinct input component and weight
 // block read once, every output component written once (read too when
