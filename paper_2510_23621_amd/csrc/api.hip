@@ -172,7 +172,7 @@ struct Buffers {
   float *w = nullptr, *wT = nullptr, *sp_table = nullptr, *sp_round = nullptr;   // (rounded copy: precision study)
   float* w_round = nullptr;   // precision study: rounded copies of the last radial layers' weights
   unsigned short *wbf = nullptr, *wbfT = nullptr;   // 16-bit K-packed copies (BF16- / FP16-linear modes)
-  unsigned short *wsp = nullptr, *wspT = nullptr;   // three bfloat16 parts of w and wT, K-packed (FP32 mode)
+  unsigned short *wsp = nullptr, *wspT = nullptr;   // three bfloat16 parts of blocks of w and wT, K-packed
   int *species = nullptr, *snd = nullptr, *rcv = nullptr, *rcv_off = nullptr, *snd_off = nullptr,
       *snd_perm = nullptr, *graph_off = nullptr, *quad_node = nullptr, *quad_species = nullptr,
       *quad_node8 = nullptr, *quad_species8 = nullptr;
@@ -712,9 +712,11 @@ void run_forward(mace_graph* h, hipStream_t s, const float* pos, float* eps, boo
       rs.n = std::min(kMaxRadialLayers, m.d.n_layers - t0);
       rs.rnd = h->rad_round;
       rs.tangent = for_forces;
+      rs.wx_part = m.split_part();
       for (int q = 0; q < rs.n; ++q) {
         const bool parts = a3_parts(h, t0 + q);
         rs.W[q] = b.w + m.off.at(std::to_string(t0 + q) + ".radial.0");
+        rs.Wx[q] = b.wsp + m.off.at(std::to_string(t0 + q) + ".radial.1");
         rs.a3[q] = b.a3[t0 + q];
         rs.t3[q] = b.t3[t0 + q];
         rs.a3x[q] = parts ? reinterpret_cast<unsigned short*>(b.a3[t0 + q]) : nullptr;
@@ -1444,9 +1446,13 @@ mace_status mace_graph_setup(const mace_model_desc* desc, const float* weights, 
   chk(hipMemsetAsync(b.status, 0, sizeof(int), s));
   launch_species_table(s, (int)S, (int)K, b.w + m.off.at("embed"), b.w + m.off.at("0.up.0"),
                        lowp_mode(prec), b.sp_table);
+  if (prec != MACE_FP64)   // split packed copies of the radial MLPs' 64 x 64 layers
+    for (int t = 0; t < m.d.n_layers; ++t)
+      launch_pack_split(s, 64, 64, 2, m.split_part(), b.w + m.off.at(std::to_string(t) + ".radial.1"),
+                        b.wsp + m.off.at(std::to_string(t) + ".radial.1"));
   if (prec == MACE_FP32) {
-    // split packed copies of every K x K block, of the composed layer-0 weights
-    // and of the factorised first layer's, and of their transposes
+    // the same of every K x K block, of the composed layer-0 weights and of the
+    // factorised first layer's, and of their transposes
     auto pack = [&](int KI, int KO, int64_t blocks, int64_t off) {
       launch_pack_split(s, KI, KO, blocks, m.split_part(), b.w + off, b.wsp + off);
       launch_pack_split(s, KO, KI, blocks, m.split_part(), b.wT + off, b.wspT + off);

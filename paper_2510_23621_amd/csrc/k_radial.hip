@@ -29,6 +29,7 @@
 // operand roles; the precision study's rounded instances run every layer on
 // FP32 MFMA with the activations as A (results: rows 4(l/16) + r of column
 // l%16).
+#include <cmath>
 #include <type_traits>
 
 #include "mace_internal.h"
@@ -38,6 +39,12 @@ namespace mace {
 typedef float f4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTE = 64;     // edges per block
+// Up to this many edges a block takes half a tile (with tangents) and one
+// interaction layer: four times the blocks, each with a quarter of the serial
+// layers, at the cost of repeating the geometry per layer. Two layers with
+// tangents: 342 edges 11 against 24 us, 82,900 edges 59 against 65; 249,000
+// edges 155 against 150, 3.1 million 2,140 against 1,850.
+constexpr int kSmallEdges = 131072;
 constexpr int kRows = 64;   // rows of a pass: 64 edges, or 32 edges and their tangents
 constexpr int kH = 64;      // hidden width
 constexpr int kPad = kH + 4;   // row pitch = 4 (mod 32): A-fragment reads hit 2 lanes per bank
@@ -113,44 +120,20 @@ __device__ __forceinline__ void hidden_rnd(const float* __restrict__ in, int ldi
 // ---- 64-wide layers on split-BF16 MFMA
 typedef unsigned short us8v __attribute__((ext_vector_type(8)));
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
-typedef unsigned u4v __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f4 mfma_b16(us8v a, us8v b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, a), __builtin_bit_cast(bf8v, b), c, 0, 0, 0);
 }
 
-// the three bfloat16 parts of eight FP32 values, element i of each operand
-// word holding value i (two values per conversion)
-__device__ __forceinline__ void split8(f4 lo, f4 hi, us8v& p0, us8v& p1, us8v& p2) {
-  u4v w0, w1, w2;
-#pragma unroll
-  for (int h = 0; h < 4; ++h) {
-    const f2v x = h < 2 ? f2v{lo[2 * h], lo[2 * h + 1]} : f2v{hi[2 * h - 4], hi[2 * h - 3]};
-    unsigned a, b, c;
-    split3_pair(x, a, b, c);
-    w0[h] = a;
-    w1[h] = b;
-    w2[h] = c;
-  }
-  p0 = __builtin_bit_cast(us8v, w0);
-  p1 = __builtin_bit_cast(us8v, w1);
-  p2 = __builtin_bit_cast(us8v, w2);
-}
-
 // A operand parts of a 64 x 64 layer for this wave's 16 columns: W[k][col] for
-// k = 32 ks + 8 (l/16) + i
-__device__ __forceinline__ void load_w_parts64(const float* __restrict__ W, us8v (&b)[2][3]) {
+// k = 32 ks + 8 (l/16) + i, from the copy split at setup ([64/8][64][8] per part)
+__device__ __forceinline__ void load_w_parts64(const unsigned short* __restrict__ W, int64_t part, us8v (&b)[2][3]) {
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int col = 16 * w + (l & 15);
-  float v[2][8];
+  const unsigned short* f = W + ((l >> 4) * kH + 16 * w + (l & 15)) * 8;
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[ks][i] = W[(32 * ks + 8 * (l >> 4) + i) * kH + col];
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks)
-    split8(f4{v[ks][0], v[ks][1], v[ks][2], v[ks][3]}, f4{v[ks][4], v[ks][5], v[ks][6], v[ks][7]}, b[ks][0], b[ks][1],
-           b[ks][2]);
+    for (int q = 0; q < 3; ++q) b[ks][q] = *reinterpret_cast<const us8v*>(f + q * part + 4 * 8 * kH * ks);
 }
 
 // ---- layers with the operands' roles swapped: A = the weights' column
@@ -231,51 +214,60 @@ __device__ __forceinline__ void store_row4(float* __restrict__ a, unsigned short
   }
 }
 
-// Edge prologue for a 64-edge tile: geometry of every edge (Y, written out, and
-// the radial basis e; the first wave computes one edge per lane in FP64), then
-// the hidden layers a3 = SiLU(SiLU(SiLU(e W0) W1) W2) of the radial MLP of
-// every interaction layer in rs, all from the same e; with TAN also a3' =
+// Edge prologue for a tile of TE edges: geometry of every edge (Y, written out,
+// and the radial basis e; the first wave computes one edge per lane in FP64),
+// then the hidden layers a3 = SiLU(SiLU(SiLU(e W0) W1) W2) of the radial MLP of
+// the interaction layers in rs, all from the same e; with TAN also a3' =
 // da3/dr from de/dr. RND: the precision study's rounding of every layer's
-// input and weights (rs.rnd: 1 bfloat16, 2 binary16).
-template <int NBP, bool TAN, bool RND>
-__global__ void __launch_bounds__(256) edge_prologue_kernel(int E, const float* __restrict__ pos,
-                                                            const int* __restrict__ snd, const int* __restrict__ rcv,
-                                                            const double4* __restrict__ shift, double rc, int p,
-                                                            int nb, float* __restrict__ Y, RadialSet rs,
-                                                            int* __restrict__ status) {
-  constexpr int NPASS = TAN ? 2 : 1, EP = kTE / NPASS;   // passes of EP edges
+// input and weights (rs.rnd: 1 bfloat16, 2 binary16). ONE: one interaction
+// layer per block (blockIdx.y), the first one's blocks write Y.
+template <int NBP, bool TAN, bool RND, int TE, bool ONE>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+edge_prologue_kernel(int E, const float* __restrict__ pos, const int* __restrict__ snd, const int* __restrict__ rcv,
+                     const double4* __restrict__ shift, RadialBasis rb, float* __restrict__ Y, RadialSet rs,
+                     int* __restrict__ status) {
+  constexpr int EP = TAN ? kRows / 2 : kRows, NPASS = TE / EP;   // passes of EP edges
+  static_assert(NPASS >= 1 && TE <= 64, "whole passes, one edge per lane of a wave");
   __shared__ float xs[NPASS * kRows * kXPad];
   // RND: two FP32 activation tiles; otherwise the three part planes
   __shared__ __align__(16) float hbuf[RND ? 2 * kRows * kPad : 3 * kPlane / 2];
   unsigned short* P = reinterpret_cast<unsigned short*>(hbuf);
-  const int e0 = blockIdx.x * kTE;
+  const int e0 = blockIdx.x * TE;
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (threadIdx.x < kTE) {
+  const int t0 = ONE ? blockIdx.y : 0, t1 = ONE ? t0 + 1 : rs.n;
+  const int nb = rb.nb;
+  // one 64-wide layer's weights in registers at a time, each requested while
+  // the values before it are still being computed
+  us8v b[2][3];
+  if constexpr (!RND) load_w_parts64(rs.Wx[t0], rs.wx_part, b);
+  if (threadIdx.x < TE) {
     const int e = e0 + threadIdx.x;
-    float row[kXPad], trow[kXPad];
+    float row[NBP], trow[NBP];
 #pragma unroll
-    for (int i = 0; i < kXPad; ++i) row[i] = trow[i] = 0.f;
+    for (int i = 0; i < NBP; ++i) row[i] = trow[i] = 0.f;
     if (e < E) {
       float y[16];
-      const int bad = edge_geometry<TAN>(e, pos, snd, rcv, shift, rc, p, nb, y, row, trow);
-      if (bad) atomicOr(status, bad);
-      float4* Yv = reinterpret_cast<float4*>(Y + (size_t)e * 16);
+      const int bad = edge_geometry<NBP, TAN>(e, pos, snd, rcv, shift, rb, y, row, trow);
+      if (t0 == 0) {
+        if (bad) atomicOr(status, bad);
+        float4* Yv = reinterpret_cast<float4*>(Y + (size_t)e * 16);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) Yv[v] = make_float4(y[4 * v], y[4 * v + 1], y[4 * v + 2], y[4 * v + 3]);
+        for (int v = 0; v < 4; ++v) Yv[v] = make_float4(y[4 * v], y[4 * v + 1], y[4 * v + 2], y[4 * v + 3]);
+      }
     }
     float* x = xs + ((threadIdx.x / EP) * kRows + threadIdx.x % EP) * kXPad;
 #pragma unroll
-    for (int i = 0; i < kXPad; ++i) {
+    for (int i = 0; i < NBP; ++i) {
       x[i] = RND ? lowp_round(row[i], rs.rnd) : row[i];
       if constexpr (TAN) x[EP * kXPad + i] = trow[i];
     }
   }
   __syncthreads();
-  for (int t = 0; t < rs.n; ++t) {
+  for (int t = t0; t < t1; ++t) {
     const float* W0 = rs.W[t];
-    const float* W1 = W0 + nb * kH;
-    const float* W2 = W1 + kH * kH;
     if constexpr (RND) {
+      const float* W1 = W0 + nb * kH;
+      const float* W2 = W1 + kH * kH;
       float* ha = hbuf;
       float* hb = hbuf + kRows * kPad;
       float b0[NBP / 4], b1[kH / 4], b2[kH / 4];
@@ -301,26 +293,29 @@ __global__ void __launch_bounds__(256) edge_prologue_kernel(int E, const float* 
       }
     } else {
       // the 64-wide layers on split-BF16 products from part planes split once
-      // by their producer; the layer's weights stay in registers over the passes
-      us8v b1[2][3], b2[2][3];
+      // by their producer. Bound by issue (67 % of the cycles vector, 28 % MFMA)
+      // beside 1.3 KB written per edge. The weights split at setup and one layer
+      // of them in registers (116 in all, four waves per SIMD in place of three)
+      // took 3.1 million edges of two layers from 2.10 to 1.85 ms, 445,000 from
+      // 0.378 to 0.315
       float b0[NBP / 4];
       load_b_frag<NBP>(W0, nb, b0);
-      load_w_parts64(W1, b1);
-      load_w_parts64(W2, b2);
 #pragma unroll
       for (int ps = 0; ps < NPASS; ++ps) {
         f4 z[4];
         input_mma_t<NBP>(xs + ps * kRows * kXPad, b0, z);
         activate<TAN>(z);
-        if (t + ps > 0) __syncthreads();   // the previous pass's reads of the planes are done
+        if (t + ps > t0) __syncthreads();   // the previous pass's reads of the planes are done
         store_parts_t(z, P);
         __syncthreads();
-        mma64_x3t(P, b1, z);
+        mma64_x3t(P, b, z);
+        load_w_parts64(rs.Wx[t] + kH * kH, rs.wx_part, b);
         activate<TAN>(z);
         __syncthreads();   // every wave has read the planes
         store_parts_t(z, P);
         __syncthreads();
-        mma64_x3t(P, b2, z);
+        mma64_x3t(P, b, z);
+        if (ps + 1 < NPASS || t + 1 < t1) load_w_parts64(rs.Wx[ps + 1 < NPASS ? t : t + 1], rs.wx_part, b);
         activate<TAN>(z);
         // four consecutive columns of one edge per lane, straight to memory
         const int c0 = 16 * w + 4 * (l >> 4);
@@ -338,11 +333,23 @@ __global__ void __launch_bounds__(256) edge_prologue_kernel(int E, const float* 
 void launch_edge_prologue(hipStream_t s, int E, const float* pos, const int* snd, const int* rcv,
                           const double4* shift, double rc, int p, int nb, float* Y, const RadialSet& rs, int* status) {
   if (E <= 0) return;
-  const int g = (E + kTE - 1) / kTE;
+  const RadialBasis rb{1.0 / rc, 3.14159265358979323846 / rc, std::sqrt(2.0 / rc), p, nb};
   auto go = [&](auto T, auto R) {
     constexpr bool TAN = decltype(T)::value, RND = decltype(R)::value;
-    if (nb <= 8) edge_prologue_kernel<8, TAN, RND><<<g, 256, 0, s>>>(E, pos, snd, rcv, shift, rc, p, nb, Y, rs, status);
-    else edge_prologue_kernel<16, TAN, RND><<<g, 256, 0, s>>>(E, pos, snd, rcv, shift, rc, p, nb, Y, rs, status);
+    auto run = [&](auto TE, auto ONE) {
+      constexpr int te = decltype(TE)::value;
+      constexpr bool one = decltype(ONE)::value;
+      const dim3 g((E + te - 1) / te, one ? rs.n : 1);
+      if (nb <= 8) edge_prologue_kernel<8, TAN, RND, te, one><<<g, 256, 0, s>>>(E, pos, snd, rcv, shift, rb, Y, rs, status);
+      else edge_prologue_kernel<16, TAN, RND, te, one><<<g, 256, 0, s>>>(E, pos, snd, rcv, shift, rb, Y, rs, status);
+    };
+    if constexpr (!RND) {
+      if (E <= kSmallEdges) {
+        run(std::integral_constant<int, TAN ? 32 : 64>{}, std::true_type{});
+        return;
+      }
+    }
+    run(std::integral_constant<int, kTE>{}, std::false_type{});
   };
   const bool tan = rs.tangent;
   if (rs.rnd) tan ? go(std::true_type{}, std::true_type{}) : go(std::false_type{}, std::true_type{});

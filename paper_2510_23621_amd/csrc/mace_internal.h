@@ -234,35 +234,47 @@ __host__ __device__ __forceinline__ void bessel_env(T r, double rc, int p, int n
   }
 }
 
-// As bessel_env (FP64), with the derivatives de_n/dr:
+// The radial basis as the kernels take it: the constants of bessel_env, which
+// are the same for every edge, from the host
+struct RadialBasis {
+  double inv_rc, pi_rc, c;   // 1/rc, pi/rc, sqrt(2/rc)
+  int p, nb;
+};
+
+// As bessel_env (FP64) for a length r with inverse inv, e_1 .. e_NBP (rb.nb <=
+// NBP; the others continue the series), with TAN also the derivatives de_n/dr:
 //   d sin(n theta)/dr = n (pi/rc) cos(n theta), cos(n theta) by the same recurrence.
-__host__ __device__ __forceinline__ void bessel_env_dr(double r, double rc, int p, int nb, double* e, double* de) {
-  const double pi = 3.14159265358979323846;
-  const double xr = r * (1.0 / rc);
-  double q = 0.5 * p * (p + 1), dq = 0.0;   // the polynomial and its derivative in x
-  for (int j = p - 2; j >= 0; --j) {
-    dq = dq * xr + q;
+template <int NBP, bool TAN>
+__device__ __forceinline__ void bessel_env_dr(double r, double inv, const RadialBasis& rb, float* e, float* de) {
+  const double xr = r * rb.inv_rc;
+  double q = 0.5 * rb.p * (rb.p + 1), dq = 0.0;   // the polynomial and its derivative in x
+  for (int j = rb.p - 2; j >= 0; --j) {
+    if constexpr (TAN) dq = dq * xr + q;
     q = q * xr + 0.5 * (j + 1) * (j + 2);
   }
   const double om = 1.0 - xr;
   double env = (om * om) * (om * q);
-  double denv = (om * om) * (om * dq - 3.0 * q) * (1.0 / rc);
+  double denv = TAN ? (om * om) * (om * dq - 3.0 * q) * rb.inv_rc : 0.0;
   if (!(xr < 1.0)) env = denv = 0.0;
-  const double c = sqrt(2.0 / rc);
-  const double pre = (c * env) / r;
-  const double dpre = (c * denv - pre) / r;
+  const double pre = (rb.c * env) * inv;
+  const double dpre = (rb.c * denv - pre) * inv;
   double s1, c1;
-  sincos(r * (pi / rc), &s1, &c1);
+  sincos(r * rb.pi_rc, &s1, &c1);
   const double c2 = 2.0 * c1;
+  const double ppi = pre * rb.pi_rc;
   double sp = 0.0, sn = s1, cp = 1.0, cn = c1;   // sin and cos of (n - 1) theta and n theta for n = 1
-  for (int n = 0; n < nb; ++n) {
-    e[n] = pre * sn;
-    de[n] = dpre * sn + pre * ((n + 1) * (pi / rc) * cn);
-    const double ns = c2 * sn - sp, nc = c2 * cn - cp;
+#pragma unroll
+  for (int n = 0; n < NBP; ++n) {
+    e[n] = (float)(pre * sn);
+    const double ns = c2 * sn - sp;
+    if constexpr (TAN) {
+      de[n] = (float)(dpre * sn + (n + 1) * ppi * cn);
+      const double nc = c2 * cn - cp;
+      cp = cn;
+      cn = nc;
+    }
     sp = sn;
     sn = ns;
-    cp = cn;
-    cn = nc;
   }
 }
 
@@ -293,15 +305,16 @@ __device__ __forceinline__ float4 edge_geometry_vjp(int e, const float* __restri
 }
 
 // Geometry of edge e in FP64, rounded to FP32 once: d = (x_snd - x_rcv) +
-// shift, r = |d|, u = d / r; Y[16] (real harmonics of u) and eb[nb] (radial
-// basis times envelope), with TAN also its derivative in r (tb[nb]). The periodic shift and the difference of wrapped
-// positions would otherwise carry FP32 rounding into every edge.
+// shift, r = |d|, u = d / r; Y[16] (real harmonics of u) and eb[NBP] (radial
+// basis times envelope), with TAN also its derivative in r (tb[NBP]). The
+// periodic shift and the difference of wrapped positions would otherwise carry
+// FP32 rounding into every edge.
 // Returns the edge's device status bits: kStatusNonFinite when d is not
 // finite, kStatusZeroLength when r = 0 (coincident atoms); 0 otherwise.
-template <bool TAN>
+template <int NBP, bool TAN>
 __device__ __forceinline__ int edge_geometry(int e, const float* __restrict__ pos, const int* __restrict__ snd,
                                              const int* __restrict__ rcv, const double4* __restrict__ shift,
-                                             double rc, int p, int nb, float* yout, float* ebout, float* tbout) {
+                                             const RadialBasis& rb, float* yout, float* ebout, float* tbout) {
   const int s = snd[e], r = rcv[e];
   const double4 sh = shift[e];
   const double dx = ((double)pos[3 * s + 0] - (double)pos[3 * r + 0]) + sh.x;
@@ -311,14 +324,9 @@ __device__ __forceinline__ int edge_geometry(int e, const float* __restrict__ po
   const double inv = 1.0 / rr;
   double y[16];
   sh16<double>(dx * inv, dy * inv, dz * inv, y);
+#pragma unroll
   for (int m = 0; m < 16; ++m) yout[m] = (float)y[m];
-  double eb[16], tb[16];
-  if constexpr (TAN) bessel_env_dr(rr, rc, p, nb, eb, tb);
-  else bessel_env<double>(rr, rc, p, nb, eb);
-  for (int n = 0; n < nb; ++n) {
-    ebout[n] = (float)eb[n];
-    if constexpr (TAN) tbout[n] = (float)tb[n];
-  }
+  bessel_env_dr<NBP, TAN>(rr, inv, rb, ebout, tbout);
   return !isfinite(rr) ? kStatusNonFinite : (rr == 0.0 ? kStatusZeroLength : 0);
 }
 
@@ -463,6 +471,9 @@ constexpr int kMaxRadialLayers = 4;
 // to kMaxRadialLayers interaction layers: a3, and with tangent set t3 = da3/dr
 struct RadialSet {
   const float* W[kMaxRadialLayers];
+  // W1, then W2, split at setup into three bfloat16 parts wx_part apart, each [64/8][64][8]
+  const unsigned short* Wx[kMaxRadialLayers];
+  int64_t wx_part;
   float *a3[kMaxRadialLayers], *t3[kMaxRadialLayers];
   // where set, the layer's a3 (t3) is written as its three bfloat16 parts
   // instead, [E][3][64] (part q of edge e at a3x + (3 e + q) 64): the bfloat16

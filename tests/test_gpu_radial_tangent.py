@@ -52,3 +52,25 @@ def test_forces_match_oracle(K, hl, nb, p, form):
         gpu = run_gpu(params, sysm, lib_blob(params, 9, STRESS_GAINS), l0_form=getattr(B, "MACE_L0_" + form),
                       radial=radial)
         assert_parity(gpu, ref, B.MACE_FP32, f"tangent K={K} hl={hl} nb={nb} p={p} {form} radial={radial}")
+
+
+@pytest.mark.parametrize("nb", [8, 9])
+def test_many_edges_match_oracle(nb):
+    """The prologue's whole tiles with every layer in one block (over 131,072
+    edges): copies of the graphs above, in place, against the oracle's one."""
+    params = model_params(4, K=32, hidden_lmax=0, n_species=3, n_bessel=nb, **STRESS)
+    one = _blobs()
+    ref = run_oracle(params, one, oracle_blob(params, 9, STRESS_GAINS))
+    M, n, G = 70, len(one.positions), one.n_graphs
+    gid = (one.graph_of_atom[None] + G * np.arange(M, dtype=np.int32)[:, None]).ravel().astype(np.int32)
+    sysm = synth.System(np.tile(one.positions, (M, 1)), np.tile(one.species, M), None, gid, M * G)
+    blob = lib_blob(params, 9, STRESS_GAINS)
+    gpu, energy = run_gpu(params, sysm, blob), run_gpu(params, sysm, blob, forces=False)
+    assert gpu["n_edges"] > 131072
+    for q in range(M):
+        part = dict(eps=gpu["eps"][n * q:n * (q + 1)], energy=gpu["energy"][G * q:G * (q + 1)],
+                    forces=gpu["forces"][n * q:n * (q + 1)])
+        if q in (0, M // 2, M - 1):
+            assert_parity(part, ref, B.MACE_FP32, f"copy {q} nb={nb}")
+        assert np.allclose(energy["eps"][n * q:n * (q + 1)], part["eps"], rtol=1e-5, atol=1e-5 * np.abs(ref["eps"]).mean())
+        assert np.linalg.norm(part["forces"] - ref["forces"]) <= 1e-5 * np.linalg.norm(ref["forces"])
