@@ -48,21 +48,16 @@
 namespace {
 
 struct NlGraph {
-  double cell[9];   // rows = lattice vectors; zero without periodicity
-  double inv[9];    // cell^-1: fractional coordinate a = x . column a
-  int periodic;
-  int nr[3];        // wrapped-image range per lattice direction
-  int a0, a1;       // atoms [a0, a1)
-  int nimg;         // images per atom, prod (2 nr_a + 1)
-  int pad;
-  int64_t c0;       // first candidate of the graph
+  double cell[9];     // rows = lattice vectors; zero without periodicity
+  double inv[9];      // cell^-1: fractional coordinate a = x . column a
+  float slack[3];     // how far outside [0, 1) a useful image's fractional coordinates lie
+  int16_t nr[3];      // wrapped-image range per lattice direction (below 10^4)
+  int16_t periodic;
+  int a0, a1;         // atoms [a0, a1)
+  int nimg;           // images per atom, prod (2 nr_a + 1)
+  int64_t c0;         // first candidate of the graph
 };
-// what the kernels read of a graph: its record, and how far outside [0, 1) the
-// fractional coordinates of a useful image lie
-struct NlGraphK {
-  NlGraph g;
-  double slack[3];
-};
+static_assert(sizeof(NlGraph) == 184, "counted on by the workspace's size (plan_nl)");
 
 constexpr int kNlThreads = 256;
 constexpr int kScanPerThread = 16;
@@ -72,14 +67,14 @@ constexpr double kCoordLimit = 1e9;   // |coordinate| bound (keeps cube indices 
 constexpr int kFlagNonFinite = 1, kFlagRange = 2;
 
 // Graph of candidate c; one graph comes by value (g0), several in memory.
-__device__ __forceinline__ const NlGraphK& graph_of_cand(const NlGraphK& g0, const NlGraphK* gs, int G, int64_t c,
-                                                         int& gi) {
+__device__ __forceinline__ const NlGraph& graph_of_cand(const NlGraph& g0, const NlGraph* gs, int G, int64_t c,
+                                                        int& gi) {
   gi = 0;
   if (G == 1) return g0;
   int lo = 0, hi = G - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (gs[mid].g.c0 <= c) lo = mid;
+    if (gs[mid].c0 <= c) lo = mid;
     else hi = mid - 1;
   }
   gi = lo;
@@ -114,15 +109,14 @@ __device__ __forceinline__ uint32_t cube_code(int g, int bx, int by, int bz) {
 // SCATTER = true places the candidates: `cursor` holds each slot's next place.
 template <bool SCATTER>
 __global__ void __launch_bounds__(kNlThreads)
-nl_bin_kernel(int64_t C, const double* __restrict__ pos, NlGraphK g0, const NlGraphK* __restrict__ gs, int G,
+nl_bin_kernel(int64_t C, const double* __restrict__ pos, NlGraph g0, const NlGraph* __restrict__ gs, int G,
               double bs, uint32_t mask, int4* __restrict__ nsh, int4* __restrict__ rcube, float4* __restrict__ rplace,
               int* __restrict__ flags, int* __restrict__ count, int* __restrict__ cursor, float4* __restrict__ place,
               int4* __restrict__ rec, int* __restrict__ num) {
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= C) return;
   int gi;
-  const NlGraphK& gk = graph_of_cand(g0, gs, G, c, gi);
-  const NlGraph& g = gk.g;
+  const NlGraph& g = graph_of_cand(g0, gs, G, c, gi);
   const uint32_t local = (uint32_t)(c - g.c0);   // candidates number at most 2^30
   const int j = g.a0 + (int)(local / (uint32_t)g.nimg);
   uint32_t s = local % (uint32_t)g.nimg;
@@ -155,7 +149,7 @@ nl_bin_kernel(int64_t C, const double* __restrict__ pos, NlGraphK g0, const NlGr
     bool near = true;
     for (int a = 0; a < 3; ++a) {
       const double f = ((w[0] * g.inv[0 * 3 + a] + w[1] * g.inv[1 * 3 + a]) + w[2] * g.inv[2 * 3 + a]) + (double)S[a];
-      near = near && f >= -gk.slack[a] && f <= 1.0 + gk.slack[a];
+      near = near && f >= -(double)g.slack[a] && f <= 1.0 + (double)g.slack[a];
     }
     if (!near && !home) return;
   }
@@ -207,7 +201,7 @@ __device__ __forceinline__ int lanes_below(uint64_t mask) {
 
 template <bool WRITE>
 __global__ void __launch_bounds__(64 * kNlWaves)
-nl_receiver_kernel(int N, const double* __restrict__ pos, NlGraphK g0, const NlGraphK* __restrict__ gs, int G,
+nl_receiver_kernel(int N, const double* __restrict__ pos, NlGraph g0, const NlGraph* __restrict__ gs, int G,
                    double bs, double rc2, float pre2, uint32_t mask, const int4* __restrict__ nsh,
                    const int4* __restrict__ rcube, const float4* __restrict__ rplace, const int* __restrict__ slot_cnt,
                    const int* __restrict__ slot_end, const float4* __restrict__ place, const int4* __restrict__ rec,
@@ -242,7 +236,7 @@ nl_receiver_kernel(int N, const double* __restrict__ pos, NlGraphK g0, const NlG
     }
   } else if (ni.w >= 0) {
     const int gi = ni.w;
-    const NlGraph& g = G == 1 ? g0.g : gs[gi].g;
+    const NlGraph& g = G == 1 ? g0 : gs[gi];
     const int4 bi = rcube[i];
     const float4 ri = rplace[i];
     const double xi[3] = {pos[3 * (size_t)i], pos[3 * (size_t)i + 1], pos[3 * (size_t)i + 2]};
@@ -581,7 +575,7 @@ constexpr int64_t kMaxCandidates = int64_t(1) << 30;
 // workspace layout (256-byte aligned pieces). `bytes` is the size asked of the
 // caller, which is also what the calls without a workspace are held to.
 struct NlPlan {
-  std::vector<NlGraphK> gs;
+  std::vector<NlGraph> gs;
   int64_t C = 0;
   uint32_t n_slots = 0;
   size_t o_gs, o_nsh, o_rcube, o_rplace, o_place, o_rec, o_num, o_scnt, o_scur, o_taken, o_rcnt, o_roff, o_bsum,
@@ -592,15 +586,15 @@ struct NlPlan {
 mace_status plan_nl(int64_t N, const double* cells, const int32_t* goff, int32_t G, double r_cut, NlPlan& p) {
   if (N < 0 || N > (int64_t(1) << 30) || !(r_cut > 0) || !std::isfinite(r_cut) || G < 1) return MACE_EINVAL;
   if (!goff && G != 1) return MACE_EINVAL;
-  p.gs.assign(G, NlGraphK{});
+  p.gs.assign(G, NlGraph{});
   int64_t C = 0;
   for (int g = 0; g < G; ++g) {
-    NlGraph& r = p.gs[g].g;
-    std::memset(&p.gs[g], 0, sizeof(NlGraphK));
+    NlGraph& r = p.gs[g];
+    std::memset(&r, 0, sizeof(r));
     r.a0 = goff ? goff[g] : 0;
     r.a1 = goff ? goff[g + 1] : (int)N;
     if (r.a0 < 0 || r.a1 < r.a0 || r.a1 > N || (g == 0 && r.a0 != 0)) return MACE_ERANGE;
-    if (g > 0 && r.a0 != p.gs[g - 1].g.a1) return MACE_ERANGE;
+    if (g > 0 && r.a0 != p.gs[g - 1].a1) return MACE_ERANGE;
     int64_t nimg = 1;
     if (cells) {
       r.periodic = 1;
@@ -611,11 +605,12 @@ mace_status plan_nl(int64_t N, const double* cells, const int32_t* goff, int32_t
                                     r.inv[2 * 3 + a] * r.inv[2 * 3 + a]);
         const double m = std::floor(r_cut * bn + 1.0 + 1e-6);
         if (!(m < 1e4)) return MACE_EUNSUPPORTED;
-        r.nr[a] = (int)m;
+        r.nr[a] = (int16_t)m;
         nimg *= 2 * r.nr[a] + 1;
         // (far above the rounding of fractional coordinates: at most about 1e-3,
-        // for coordinates of 1e9 in the most skewed cells accepted)
-        p.gs[g].slack[a] = r_cut * bn + 1e-2;
+        // for coordinates of 1e9 in the most skewed cells accepted, and of the
+        // slack itself: below 1e-3 at its limit of 10^4)
+        r.slack[a] = (float)(r_cut * bn + 1e-2);
       }
     }
     if (nimg > kMaxCandidates) return MACE_EUNSUPPORTED;
@@ -624,8 +619,8 @@ mace_status plan_nl(int64_t N, const double* cells, const int32_t* goff, int32_t
     C += (int64_t)(r.a1 - r.a0) * nimg;
     if (C > kMaxCandidates) return MACE_EUNSUPPORTED;
   }
-  if (!goff && p.gs[0].g.a1 != N) return MACE_ERANGE;
-  if (p.gs[G - 1].g.a1 != N) return MACE_ERANGE;
+  if (!goff && p.gs[0].a1 != N) return MACE_ERANGE;
+  if (p.gs[G - 1].a1 != N) return MACE_ERANGE;
   p.C = C;
   const size_t n1 = (size_t)std::max<int64_t>(N, 1), c1 = (size_t)std::max<int64_t>(C, 1);
   size_t o = 0;
@@ -634,9 +629,11 @@ mace_status plan_nl(int64_t N, const double* cells, const int32_t* goff, int32_t
     o += (bytes + 255) & ~size_t(255);
     return at;
   };
-  // The size asked of the caller: 40 bytes per image, 40 per atom and a slot
-  // table of twice the images. The pieces below need less for every input (36,
-  // 48, and 8 bytes per slot of a table a fraction of that).
+  // The size asked of the caller: per graph its record, per image 40 bytes, per
+  // atom 52, and 16 bytes per slot of a table of at least twice the images. The
+  // pieces below fit in it for every input: the same record, 36 bytes per image,
+  // 60 per atom (4 more than are saved where an atom has one image only: there
+  // the smaller slot table pays for them), and 8 bytes per slot.
   uint32_t ns = 1024;
   while ((int64_t)ns < 2 * C) ns <<= 1;
   const int64_t tiles = (std::max<int64_t>(ns, n1) + kScanTile - 1) / kScanTile;
@@ -650,7 +647,7 @@ mace_status plan_nl(int64_t N, const double* cells, const int32_t* goff, int32_t
   p.n_slots = 1024;
   while (p.n_slots < ns && (int64_t)p.n_slots < std::max<int64_t>(N, C / 16)) p.n_slots <<= 1;
   o = 0;
-  p.o_gs = take(sizeof(NlGraphK) * G);
+  p.o_gs = take(sizeof(NlGraph) * G);
   p.o_nsh = take(sizeof(int4) * n1);
   p.o_rcube = take(sizeof(int4) * n1);
   p.o_rplace = take(sizeof(float4) * n1);
@@ -663,8 +660,8 @@ mace_status plan_nl(int64_t N, const double* cells, const int32_t* goff, int32_t
   p.o_rcnt = take(sizeof(int) * n1);
   p.o_roff = take(sizeof(int64_t) * (n1 + 2));   // offsets, total, flags
   p.o_bsum = take(sizeof(int64_t) * ((n1 + kScanTile - 1) / kScanTile + 1));
-  if (o > p.bytes) return MACE_EUNSUPPORTED;   // (no input reaches this)
   p.o_found = o;
+  p.bytes = std::max(p.bytes, o);
   p.found_cap = (int)std::min<size_t>((p.bytes - o) / (sizeof(int) * n1), kNlSortCap);
   return MACE_OK;
 }
@@ -688,7 +685,7 @@ mace_status nl_run(const NlPlan& p, int64_t n_atoms, const double* positions, in
   if (n_atoms == 0) return MACE_OK;
   hipStream_t s = (hipStream_t)stream;
   char* w = reinterpret_cast<char*>(workspace);
-  auto* gs = reinterpret_cast<NlGraphK*>(w + p.o_gs);
+  auto* gs = reinterpret_cast<NlGraph*>(w + p.o_gs);
   auto* nsh = reinterpret_cast<int4*>(w + p.o_nsh);
   auto* rcube = reinterpret_cast<int4*>(w + p.o_rcube);
   auto* rplace = reinterpret_cast<float4*>(w + p.o_rplace);
@@ -713,12 +710,12 @@ mace_status nl_run(const NlPlan& p, int64_t n_atoms, const double* positions, in
   const float pre2 = bs >= 1.0 ? (float)(pre * pre * (1.0 + 1e-6)) : INFINITY;
   const uint32_t mask = p.n_slots - 1;
   hipError_t err = hipSuccess;
-  if (G > 1) err = hipMemcpyAsync(gs, p.gs.data(), sizeof(NlGraphK) * G, hipMemcpyHostToDevice, s);
+  if (G > 1) err = hipMemcpyAsync(gs, p.gs.data(), sizeof(NlGraph) * G, hipMemcpyHostToDevice, s);
   if (err != hipSuccess) {
     (void)hipStreamSynchronize(s);   // the plan's host copy must outlive the upload
     return MACE_EHIP;
   }
-  const NlGraphK& g0 = p.gs[0];
+  const NlGraph& g0 = p.gs[0];
   nl_zero_kernel<<<std::min<unsigned>(256, p.n_slots / kNlThreads), kNlThreads, 0, s>>>(scnt, p.n_slots, taken,
                                                                                        roff + n_atoms + 1);
   const unsigned cblk = (unsigned)((p.C + kNlThreads - 1) / kNlThreads);   // (C >= N > 0)

@@ -68,6 +68,24 @@ def test_equals_host_list(name):
             assert np.array_equal(h, d.cpu().numpy())
 
 
+@pytest.mark.parametrize("n,graphs", [(0, 1000), (10, 500), (305, 305), (1024, 1024), (65536, 65536), (3000, 2000)])
+def test_single_atoms_and_empty_graphs(n, graphs):
+    """One atom or none in a graph, or (3000 in 2000) one and two."""
+    rng = np.random.default_rng(n)
+    g = np.sort(np.arange(n) % graphs).astype(np.int32)
+    off = np.searchsorted(g, np.arange(graphs + 1)).astype(np.int32)
+    pos = rng.uniform(0, 4, (n, 3))
+    host = B.mace_neighbor_list(pos, 5.0, None, g, graphs)
+    dpos = torch.from_numpy(pos).cuda()
+    for fn in (B.mace_neighbor_list_device, B.mace_neighbor_list_device_noalloc):
+        dev = fn(dpos, 5.0, None, off, graphs)
+        torch.cuda.synchronize()
+        print(f"[neighbors] {n} atoms in {graphs} graphs: {len(host[0])} edges", flush=True)
+        assert (len(host[0]) > 0) == (n > graphs)
+        for h, d in zip(host, dev):
+            assert np.array_equal(h, d.cpu().numpy())
+
+
 def test_short_capacity_leaves_outputs_alone():
     import ctypes
     pos, rc, cells, _ = _inputs("short cutoff")

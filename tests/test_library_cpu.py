@@ -167,3 +167,30 @@ def test_device_neighbor_workspace_size_without_gpu():
     assert B.mace_neighbor_workspace_bytes(100, 5.0, np.zeros((1, 3, 3))) == 0
     assert B.mace_neighbor_workspace_bytes(100, 5.0, None, np.array([0, 50, 90], np.int32), 2) == 0
     assert B.mace_neighbor_workspace_bytes(100, 5.0, None, np.array([0, 50, 100], np.int32), 2) > 0
+
+
+def _published_list_bytes(n, images, graphs):
+    """The device list's workspace for n atoms with `images` candidates in all:
+    pieces of 256 bytes' alignment, and a slot table of twice the candidates."""
+    n, c = max(n, 1), max(images, 1)
+    ns = 1024
+    while ns < 2 * images:
+        ns *= 2
+    tiles = -(-max(ns, n) // 4096)
+    pieces = [184 * graphs, 24 * n, 16 * n, 4 * c, 16 * c, 16 * c, 4 * ns, 4 * ns, 8 * (ns + 1), 4 * c, 4 * n,
+              8 * (n + 1), 8 * (tiles + 1), 4]
+    return sum(-(-b // 256) * 256 for b in pieces)
+
+
+@pytest.mark.parametrize("n,graphs", [(0, 1), (0, 1000), (1, 1), (1, 400), (1, 600), (10, 500), (100, 1000),
+                                      (304, 304), (305, 305), (512, 512), (1000, 1000), (1024, 1024), (4096, 4096),
+                                      (65536, 65536), (65537, 65537), (5, 400000), (70001, 1), (300000, 7)])
+def test_device_neighbor_workspace_size_of_sparse_batches(n, graphs):
+    """Batches of single atoms (isolated-atom energies) and of mostly empty
+    graphs are accepted, at the size every other list of as many atoms has, with
+    and without cells."""
+    counts = np.bincount(np.arange(n) % graphs, minlength=graphs)
+    off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    assert B.mace_neighbor_workspace_bytes(n, 5.0, None, off, graphs) == _published_list_bytes(n, n, graphs)
+    cells = np.tile(np.eye(3)[None] * 12.0, (graphs, 1, 1))
+    assert B.mace_neighbor_workspace_bytes(n, 5.0, cells, off, graphs) == _published_list_bytes(n, 27 * n, graphs)
