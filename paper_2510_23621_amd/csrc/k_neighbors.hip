@@ -341,7 +341,8 @@ nl_receiver_kernel(int N, const double* __restrict__ pos, NlGraph g0, const NlGr
       const Step now = st;
       more = next(st);
       const float dx = now.v.x + now.sx, dy = now.v.y + now.sy, dz = now.v.z + now.sz;
-      const bool pass = now.at >= 0 && __float_as_uint(now.v.w) == now.code && (dx * dx + dy * dy) + dz * dz < pre2;
+      // (not >=: a place beyond FP32, where the cutoff is, gives NaN and goes to the exact test)
+      const bool pass = now.at >= 0 && __float_as_uint(now.v.w) == now.code && !((dx * dx + dy * dy) + dz * dz >= pre2);
       const uint64_t bal = __ballot(pass);
       if (pass) s_list[w][listed + lanes_below(bal)] = now.at;
       listed += __popcll(bal);

@@ -42,6 +42,8 @@ def _inputs(name):
         n = rng.integers(0, 5, 900)
         g = np.repeat(np.arange(900), n).astype(np.int32)
         return rng.uniform(0, 40, (len(g), 3)), 20.0, None, g
+    if name == "cutoff beyond FP32":   # every pair, on both sides of the origin
+        return rng.uniform(-30, 30, (50, 3)), 1e39, None, None
     if name == "on the cutoff":       # pairs at the cutoff exactly (left out) and one step inside
         x = np.arange(40) * 1.5
         return np.stack([x, np.zeros(40), np.zeros(40)], 1), 4.5, None, None
@@ -49,7 +51,7 @@ def _inputs(name):
 
 
 @pytest.mark.parametrize("name", ["cells of their own", "many atoms", "short cutoff", "far away", "many cells away",
-                                  "many small graphs", "on the cutoff"])
+                                  "many small graphs", "on the cutoff", "cutoff beyond FP32"])
 def test_equals_host_list(name):
     pos, rc, cells, g = _inputs(name)
     G = 1 if g is None else int(g.max()) + 1
