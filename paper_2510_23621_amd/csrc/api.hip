@@ -39,6 +39,7 @@ struct LayerPlan {
   std::vector<so3h::Path> paths;
   int P = 0, mid = 0, din = 0, dout = 0, lh_max = 0, lout_max = 0;
   std::vector<int> path_off;
+  int64_t w3_off = 0;   // of its last radial layer among all layers' (Model::w3_total)
 };
 
 struct Model {
@@ -53,6 +54,7 @@ struct Model {
   int64_t l0_off = 0;      // after those: its weights [4][S][l0_ki][K] (transposed copy [4][S][K][l0_ki])
   int64_t total_ext = 0;   // blob + combined weights (FP32 copies only)
   int64_t split_part() const { return (total_ext + 7) / 8 * 8; }   // elements of one part of the split copies
+  int64_t w3_total = 0;    // elements of the last radial layers together (layer t's begin at LayerPlan::w3_off)
   int max_P = 0, max_mid = 0, max_din = 0, max_dout = 0;
 };
 
@@ -117,6 +119,8 @@ mace_status build_model(const mace_model_desc* desc, Model& m) {
     const int64_t h[4] = {d.n_bessel, 64, 64, 64};
     for (int i = 0; i < 3; ++i) add(pre + "radial." + std::to_string(i), {h[i], h[i + 1]}, h[i]);
     add(pre + "radial.3", {64, (int64_t)L.P * K}, 64);
+    L.w3_off = m.w3_total;
+    m.w3_total += 64 * (int64_t)L.P * K;
     for (int p = 0; p < L.P; ++p) {
       int nin = 0;
       for (auto& q : L.paths) nin += (q.lo == L.paths[p].lo);
@@ -170,9 +174,10 @@ struct Carver {
 
 struct Buffers {
   float *w = nullptr, *wT = nullptr, *sp_table = nullptr, *sp_round = nullptr;   // (rounded copy: precision study)
-  float* w_round = nullptr;   // precision study: rounded copies of the last radial layers' weights
-  unsigned short *wbf = nullptr, *wbfT = nullptr;   // 16-bit K-packed copies (BF16- / FP16-linear modes)
-  unsigned short *wsp = nullptr, *wspT = nullptr;   // three bfloat16 parts of blocks of w and wT, K-packed
+  float* w3_round = nullptr;   // precision study: rounded copies of the last radial layers' weights
+  unsigned short *wbf = nullptr, *wbfT = nullptr;   // BF16- / FP16-linear modes: 16-bit K-packed copies
+  unsigned short *wsp = nullptr, *wspT = nullptr;   // FP32 mode: three bfloat16 parts of blocks of w and wT, K-packed
+  unsigned short* wrad = nullptr;   // per layer, the same parts of the radial MLP's 64 x 64 layers, kRadPart apart
   int *species = nullptr, *snd = nullptr, *rcv = nullptr, *rcv_off = nullptr, *snd_off = nullptr,
       *snd_perm = nullptr, *graph_off = nullptr, *quad_node = nullptr, *quad_species = nullptr,
       *quad_node8 = nullptr, *quad_species8 = nullptr;
@@ -203,17 +208,29 @@ int64_t n_tiles_bound(int64_t N, int S) { return (N + kLinTileNodes - 1) / kLinT
 // every graph has at least one chunk; a graph of n edges has ceil(n / kStressChunk)
 int64_t stress_chunk_bound(int64_t E, int G) { return G + E / kStressChunk + 1; }
 
-void carve(const Model& m, int64_t N, int64_t E, int G, Carver& c, Buffers& b) {
+// rounding mode of the channel-mixing linears: 0 FP32, 1 bfloat16, 2 binary16
+int lowp_mode(mace_precision p) {
+  return (p == MACE_BF16_LINEAR || p == MACE_BF16_RADIAL) ? 1 : (p == MACE_FP16_LINEAR ? 2 : 0);
+}
+
+constexpr int64_t kRadPart = 2 * 64 * 64;   // elements of one part of a layer's two 64 x 64 radial layers
+
+void carve(const Model& m, int64_t N, int64_t E, int G, mace_precision prec, Carver& c, Buffers& b) {
   const int64_t K = m.d.K, S = m.d.n_species, T = m.d.n_layers;
   b.w = c.take<float>(m.total_ext);
   b.wT = c.take<float>(m.total_ext);
-  b.wbf = c.take<unsigned short>(m.total);
-  b.wbfT = c.take<unsigned short>(m.total);
-  b.wsp = c.take<unsigned short>(3 * m.split_part());
-  b.wspT = c.take<unsigned short>(3 * m.split_part());
+  if (lowp_mode(prec)) {
+    b.wbf = c.take<unsigned short>(m.total);
+    b.wbfT = c.take<unsigned short>(m.total);
+  }
+  if (prec == MACE_FP32) {
+    b.wsp = c.take<unsigned short>(3 * m.split_part());
+    b.wspT = c.take<unsigned short>(3 * m.split_part());
+  }
+  if (prec != MACE_FP64) b.wrad = c.take<unsigned short>(3 * kRadPart * T);
   b.sp_table = c.take<float>(S * K);
   b.sp_round = c.take<float>(S * K);
-  b.w_round = c.take<float>(m.total_ext);
+  b.w3_round = c.take<float>(m.w3_total);
   b.species = c.take<int>(N);
   b.snd = c.take<int>(std::max<int64_t>(E, 1));
   b.rcv = c.take<int>(std::max<int64_t>(E, 1));
@@ -406,6 +423,12 @@ int radial_mode(const mace_graph* h) { return h->prec == MACE_BF16_RADIAL ? 1 : 
 // the prologue writes (part 0 is the bfloat16 rounding).
 bool a3_parts(const mace_graph* h, int t) { return radial_mode(h) != 0 && !layer_factorised(h, t); }
 
+// The weights of layer t's last radial layer as its edge products read them.
+const float* last_radial(const mace_graph* h, int t) {
+  return h->rad_round ? h->b.w3_round + h->m.layers[t].w3_off
+                      : h->b.w + h->m.off.at(std::to_string(t) + ".radial.3");
+}
+
 // Every edge product the handle's settings will launch has a kernel instance
 // (checked before anything is enqueued; the launchers check again).
 bool launchable(const mace_graph* h) {
@@ -428,11 +451,6 @@ void run_linear(mace_graph* h, hipStream_t s, const LinPlanRef& P, const LinArgs
 }
 
 mace_status hip_ok(hipError_t e) { return e == hipSuccess ? MACE_OK : MACE_EHIP; }
-
-// rounding mode of the channel-mixing linears: 0 FP32, 1 bfloat16, 2 binary16
-int lowp_mode(mace_precision p) {
-  return (p == MACE_BF16_LINEAR || p == MACE_BF16_RADIAL) ? 1 : (p == MACE_FP16_LINEAR ? 2 : 0);
-}
 
 // The 16-bit modes' factorised first layer runs its three linears (the FP32
 // contraction, then the 16-bit path-merging and species linears; backward,
@@ -712,11 +730,11 @@ void run_forward(mace_graph* h, hipStream_t s, const float* pos, float* eps, boo
       rs.n = std::min(kMaxRadialLayers, m.d.n_layers - t0);
       rs.rnd = h->rad_round;
       rs.tangent = for_forces;
-      rs.wx_part = m.split_part();
+      rs.wx_part = kRadPart;
       for (int q = 0; q < rs.n; ++q) {
         const bool parts = a3_parts(h, t0 + q);
         rs.W[q] = b.w + m.off.at(std::to_string(t0 + q) + ".radial.0");
-        rs.Wx[q] = b.wsp + m.off.at(std::to_string(t0 + q) + ".radial.1");
+        rs.Wx[q] = b.wrad + 3 * kRadPart * (t0 + q);
         rs.a3[q] = b.a3[t0 + q];
         rs.t3[q] = b.t3[t0 + q];
         rs.a3x[q] = parts ? reinterpret_cast<unsigned short*>(b.a3[t0 + q]) : nullptr;
@@ -729,12 +747,10 @@ void run_forward(mace_graph* h, hipStream_t s, const float* pos, float* eps, boo
   }
   if (h->rad_round) {
     // precision study: the last radial layer (inside the edge products) reads rounded weights
-    for (int t = 0; t < m.d.n_layers; ++t) {
-      const int64_t o = m.off.at(std::to_string(t) + ".radial.3");
-      launch_round(s, b.w_round + o, b.w + o, (size_t)64 * m.layers[t].P * K, h->rad_round);
-    }
+    for (int t = 0; t < m.d.n_layers; ++t)
+      launch_round(s, b.w3_round + m.layers[t].w3_off, b.w + m.off.at(std::to_string(t) + ".radial.3"),
+                   (size_t)64 * m.layers[t].P * K, h->rad_round);
   }
-  const float* wr3 = h->rad_round ? b.w_round : b.w;
   if (h->tp_round) {
     // precision study: the edge products read rounded harmonics and sender features
     launch_round(s, b.Y, b.Y, (size_t)E * 16, h->tp_round);
@@ -773,7 +789,7 @@ void run_forward(mace_graph* h, hipStream_t s, const float* pos, float* eps, boo
       }
       {
         PROF(KID_TP_FWD);
-        (void)launch_tpr_fwd(s, L.lh_max, N, K, b.rcv_off, b.snd, src_map, b.a3[t], wr3 + m.off.at(pre + "radial.3"),
+        (void)launch_tpr_fwd(s, L.lh_max, N, K, b.rcv_off, b.snd, src_map, b.a3[t], last_radial(h, t),
                        b.Y, src, inv_c, b.At, radial_mode(h), h->tp_round);
       }
       if (t == 0 && !lowp) {
@@ -871,8 +887,8 @@ void run_backward(mace_graph* h, hipStream_t s, const float* pos, float* F, cons
       const int* src_map = t == 0 ? b.species : nullptr;
       PROF(KID_TP_BWD);
       (void)launch_tpr_bwd(s, L.lh_max, N, K, E, b.rcv_off, b.snd, src_map, b.a3[t], b.t3[t],
-                     (h->rad_round ? b.w_round : b.w) + m.off.at(pre + "radial.3"),
-                     b.Y, src, inv_c, b.dAt, rows, t > 0 ? b.Q : nullptr, radial_mode(h), h->tp_round);
+                           last_radial(h, t), b.Y, src, inv_c, b.dAt, rows, t > 0 ? b.Q : nullptr, radial_mode(h),
+                           h->tp_round);
     }
     if (t > 0) {
       PROF(KID_SENDER_SUM);
@@ -1095,7 +1111,7 @@ size_t mace_workspace_bytes(const mace_model_desc* desc, int64_t n_atoms, int64_
   if (build_model(desc, m) != MACE_OK || n_atoms < 1 || n_edges < 0 || n_graphs < 1) return 0;
   Carver c{nullptr};
   Buffers b;
-  carve(m, n_atoms, n_edges, n_graphs, c, b);
+  carve(m, n_atoms, n_edges, n_graphs, prec, c, b);
   if (prec == MACE_FP64) {
     Buffers64 b64;
     carve64(m, n_atoms, n_edges, c, b64);
@@ -1312,10 +1328,11 @@ mace_status mace_graph_setup(const mace_model_desc* desc, const float* weights, 
     }
   }
 
-  // 16-bit copies (bf16 or binary16, by mode) of every K x K block, packed
+  // 16-bit modes: copies (bf16 or binary16) of every K x K block, packed
   // [K/8][K][8] (element (k, n) at ((k/8) K + n) 8 + k%8) for the MFMA B
   // operand of the 16-bit linears
-  std::vector<uint16_t> hbf(m.total, 0), hbfT(m.total, 0);
+  const int64_t n16 = lowp_mode(prec) ? m.total : 0;
+  std::vector<uint16_t> hbf(n16, 0), hbfT(n16, 0);
   auto to_bf16 = [](float x) -> uint16_t {
     uint32_t u;
     std::memcpy(&u, &x, 4);
@@ -1331,7 +1348,7 @@ mace_status mace_graph_setup(const mace_model_desc* desc, const float* weights, 
   };
   for (auto& t : m.tensors) {
     const auto& sh = t.shape;
-    if (!(sh.size() >= 2 && sh[sh.size() - 1] == K && sh[sh.size() - 2] == K)) continue;
+    if (!n16 || !(sh.size() >= 2 && sh[sh.size() - 1] == K && sh[sh.size() - 2] == K)) continue;
     const int64_t blocks = t.size() / (K * K);
     for (int64_t q = 0; q < blocks; ++q) {
       const int64_t base = t.offset + q * K * K;
@@ -1389,7 +1406,7 @@ mace_status mace_graph_setup(const mace_model_desc* desc, const float* weights, 
   // the buffers are carved from the workspace base rounded up to 256 bytes
   // (mace_workspace_bytes includes that slack)
   Carver c{reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(workspace) + 255) & ~uintptr_t(255))};
-  carve(h->m, N, E, G, c, h->b);
+  carve(h->m, N, E, G, prec, c, h->b);
   if (prec == MACE_FP64) carve64(h->m, N, E, c, h->b64);
   Buffers& b = h->b;
   auto up = [&](void* dst, const void* src, size_t bytes) {
@@ -1399,8 +1416,8 @@ mace_status mace_graph_setup(const mace_model_desc* desc, const float* weights, 
   auto chk = [&](hipError_t e) { if (e != hipSuccess && err == hipSuccess) err = e; };
   chk(up(b.w, hw.data(), m.total_ext * 4));
   chk(up(b.wT, hwT.data(), m.total_ext * 4));
-  chk(up(b.wbf, hbf.data(), m.total * 2));
-  chk(up(b.wbfT, hbfT.data(), m.total * 2));
+  chk(up(b.wbf, hbf.data(), n16 * 2));
+  chk(up(b.wbfT, hbfT.data(), n16 * 2));
   chk(up(b.species, hs.data(), N * 4));
   chk(up(b.snd, hsnd, E * 4));
   chk(up(b.rcv, hrcv, E * 4));
@@ -1448,8 +1465,8 @@ mace_status mace_graph_setup(const mace_model_desc* desc, const float* weights, 
                        lowp_mode(prec), b.sp_table);
   if (prec != MACE_FP64)   // split packed copies of the radial MLPs' 64 x 64 layers
     for (int t = 0; t < m.d.n_layers; ++t)
-      launch_pack_split(s, 64, 64, 2, m.split_part(), b.w + m.off.at(std::to_string(t) + ".radial.1"),
-                        b.wsp + m.off.at(std::to_string(t) + ".radial.1"));
+      launch_pack_split(s, 64, 64, 2, kRadPart, b.w + m.off.at(std::to_string(t) + ".radial.1"),
+                        b.wrad + 3 * kRadPart * t);
   if (prec == MACE_FP32) {
     // the same of every K x K block, of the composed layer-0 weights and of the
     // factorised first layer's, and of their transposes

@@ -194,3 +194,22 @@ def test_device_neighbor_workspace_size_of_sparse_batches(n, graphs):
     assert B.mace_neighbor_workspace_bytes(n, 5.0, None, off, graphs) == _published_list_bytes(n, n, graphs)
     cells = np.tile(np.eye(3)[None] * 12.0, (graphs, 1, 1))
     assert B.mace_neighbor_workspace_bytes(n, 5.0, cells, off, graphs) == _published_list_bytes(n, 27 * n, graphs)
+
+
+@pytest.mark.parametrize("shape,fp32,fp64", [
+    ((10, 128, 2, 1, 20, 300), 33121280, 50233472), ((2, 128, 2, 2, 20, 300), 22696960, 39518336),
+    ((2, 32, 2, 0, 20, 300), 2799360, 5174912), ((4, 96, 3, (2, 1), 100, 0), 36613632, 68543520),
+    ((10, 64, 8, 2, 20, 300), 46201088, 76114816)])
+def test_workspace_of_small_graphs_is_the_modes_own(shape, fp32, fp64):
+    """On a small graph the weights' copies are the workspace. The three
+    bfloat16 parts of the linears' weights belong to MACE_FP32 alone: in every
+    other mode a handle takes no more than one without any split copies did
+    (fp32, the same in all modes but FP64, and fp64), in MACE_FP32 12 bytes more
+    per weight (the first layer's composed blocks among them) at most."""
+    S, K, T, hl, N, E = shape
+    desc = B.make_desc(n_species=S, K=K, hidden_lmax=hl, r_cut=5.0, c_norm=1.0, n_layers=T)
+    for prec, bound in ((B.MACE_BF16_LINEAR, fp32), (B.MACE_FP16_LINEAR, fp32), (B.MACE_BF16_RADIAL, fp32),
+                        (B.MACE_FP64, fp64)):
+        assert 0 < B.mace_workspace_bytes(desc, N, E, 1, prec) <= bound
+    weights = B.mace_weight_layout(desc)[1] + 4 * S * K * K + (4 * S * 64 * S * K if S <= 4 else 0)
+    assert 0 < B.mace_workspace_bytes(desc, N, E, 1, B.MACE_FP32) <= fp32 + 12 * weights
