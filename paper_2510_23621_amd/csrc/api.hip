@@ -187,12 +187,16 @@ struct Buffers {
   // their three bfloat16 parts [E][3][64] where the layer's edge products take
   // bfloat16 operands (one buffer, sized for the parts)
   std::vector<float*> a3, t3;
+  // per layer: the backward's gradient rows [K/16][E][16], dE/dr and dE/dY[1..15]
+  // per channel tile. Those of layer t lie in a3 and t3 of layer t + 1 (at most
+  // K = 128 of their 192 floats per edge), which that layer's backward has read
+  // for the last time; the last layer's have a place of their own.
+  std::vector<float*> rows;
   std::vector<float*> A, hin, ht;
   float *hlast = nullptr, *sc = nullptr, *At = nullptr, *Apre = nullptr, *B = nullptr;
   // backward
   float *dh0 = nullptr, *dh1 = nullptr, *dB = nullptr, *dA = nullptr, *dApre = nullptr, *dAt = nullptr,
         *Q = nullptr, *dht = nullptr;
-  float* dYp = nullptr;   // gradient rows [T K/16][E][16]: dE/dr and dE/dY[1..15] per layer and channel tile
   float *U0 = nullptr, *gU0 = nullptr;     // factorised first layer: U and dE/dU, [N][16][l0_ki]
   int* snd_z = nullptr;                    // [E] species of each edge's sender
   float4* g = nullptr;
@@ -213,6 +217,7 @@ int lowp_mode(mace_precision p) {
   return (p == MACE_BF16_LINEAR || p == MACE_BF16_RADIAL) ? 1 : (p == MACE_FP16_LINEAR ? 2 : 0);
 }
 
+constexpr int kEdgeFloats = 192;   // floats per edge of a layer's a3 and t3, as three bfloat16 parts [3][64] each
 constexpr int64_t kRadPart = 2 * 64 * 64;   // elements of one part of a layer's two 64 x 64 radial layers
 
 void carve(const Model& m, int64_t N, int64_t E, int G, mace_precision prec, Carver& c, Buffers& b) {
@@ -247,13 +252,19 @@ void carve(const Model& m, int64_t N, int64_t E, int G, mace_precision prec, Car
   b.Y = c.take<float>(std::max<int64_t>(E, 1) * 16);
   b.a3.resize(T);
   b.t3.resize(T);
+  b.rows.resize(T);
+  const size_t E1 = std::max<int64_t>(E, 1);
+  float* edge = c.take<float>(E1 * (kEdgeFloats * T + K));   // layer t's a3 and t3, then the last layer's rows
+  for (int t = 0; edge && t < T; ++t) {
+    b.a3[t] = edge + E1 * kEdgeFloats * t;
+    b.t3[t] = b.a3[t] + E1 * (kEdgeFloats / 2);
+    b.rows[t] = b.a3[t] + E1 * kEdgeFloats;
+  }
   b.A.resize(T);
   b.hin.assign(T, nullptr);
   b.ht.assign(T, nullptr);
   for (int t = 0; t < T; ++t) {
     const LayerPlan& L = m.layers[t];
-    b.a3[t] = c.take<float>(std::max<int64_t>(E, 1) * 96);
-    b.t3[t] = c.take<float>(std::max<int64_t>(E, 1) * 96);
     b.A[t] = c.take<float>(N * 16 * K);
     if (t > 0) {
       b.hin[t] = c.take<float>(N * L.din * K);
@@ -272,7 +283,6 @@ void carve(const Model& m, int64_t N, int64_t E, int G, mace_precision prec, Car
   b.dA = c.take<float>(N * 16 * K);
   b.dApre = c.take<float>(N * 16 * K);
   b.dAt = c.take<float>(N * m.max_mid * K);
-  b.dYp = c.take<float>(T * (K / 16) * std::max<int64_t>(E, 1) * 16);
   b.Q = c.take<float>(std::max<int64_t>(E, 1) * m.max_din * K);
   b.dht = c.take<float>(N * m.max_din * K);
   b.g = c.take<float4>(std::max<int64_t>(E, 1));
@@ -840,7 +850,8 @@ void run_backward(mace_graph* h, hipStream_t s, const float* pos, float* F, cons
   const float inv_c = (float)(1.0 / m.d.c_norm);
   float* dnext = b.dh0;
   float* dprev = b.dh1;
-  int n_rows = 0;   // gradient rows written so far
+  // the layers' gradient rows, last layer first
+  GradRows gr{b.rows[T - 1], (int64_t)kEdgeFloats * E, K / 16, 0};
   for (int t = T - 1; t >= 0; --t) {
     const LayerPlan& L = m.layers[t];
     const std::string pre = std::to_string(t) + ".";
@@ -876,8 +887,8 @@ void run_backward(mace_graph* h, hipStream_t s, const float* pos, float* F, cons
     }
     // the layer's gradient rows (dE/dr and dE/dY per edge): one per channel
     // tile, or whole from the factorised first layer
-    float* rows = b.dYp + (size_t)n_rows * E * 16;
-    n_rows += fact ? 1 : K / 16;
+    float* rows = b.rows[t];
+    gr.n += fact ? 1 : K / 16;
     if (fact) {
       PROF(KID_L0_BWD);
       launch_l0_edge_bwd(s, N, m.d.n_species, b.rcv_off, b.snd_z, b.a3[0], b.t3[0], b.Y, b.gU0,
@@ -905,7 +916,7 @@ void run_backward(mace_graph* h, hipStream_t s, const float* pos, float* F, cons
   }
   {
     PROF(KID_EDGE_BWD);
-    launch_edge_vjp(s, E, pos, b.snd, b.rcv, b.shift, b.dYp, n_rows, b.g);
+    launch_edge_vjp(s, E, pos, b.snd, b.rcv, b.shift, gr, b.g);
   }
   {
     PROF(KID_FORCES);

@@ -6,12 +6,11 @@
 
 namespace mace {
 
-// g = dE/dd per edge from its gradient rows (n_part partials dYp[part][E][16],
-// summed in part order): one thread per edge, FP64.
+// g = dE/dd per edge from its gradient rows (every layer's partials, summed in
+// order): one thread per edge, FP64.
 __global__ void __launch_bounds__(256) edge_vjp_kernel(int E, const float* __restrict__ pos,
                                                        const int* __restrict__ snd, const int* __restrict__ rcv,
-                                                       const double4* __restrict__ shift,
-                                                       const float* __restrict__ dYp, int n_part,
+                                                       const double4* __restrict__ shift, GradRows rows,
                                                        float4* __restrict__ g) {
   typedef float f4 __attribute__((ext_vector_type(4)));
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
@@ -19,11 +18,19 @@ __global__ void __launch_bounds__(256) edge_vjp_kernel(int E, const float* __res
   f4 s[4];
 #pragma unroll
   for (int v = 0; v < 4; ++v) s[v] = f4{0.f, 0.f, 0.f, 0.f};
+  // one flat loop over all layers' partials, so that four rows' loads are in
+  // flight whatever the number per layer (a loop per layer: 1.3 us more for one
+  // molecule, 0.8 us for 96 atoms)
+  const float* layer = rows.first;
+  int c = 0;
 #pragma unroll 4
-  for (int q = 0; q < n_part; ++q) {
-    const f4* row = reinterpret_cast<const f4*>(dYp + ((size_t)q * E + e) * 16);
+  for (int q = 0; q < rows.n; ++q) {
+    const f4* row = reinterpret_cast<const f4*>(layer + ((size_t)c * E + e) * 16);
 #pragma unroll
     for (int v = 0; v < 4; ++v) s[v] += row[v];
+    const bool next = ++c == rows.parts;
+    c = next ? 0 : c;
+    layer -= next ? rows.step : 0;
   }
   float dy[16];
 #pragma unroll
@@ -156,9 +163,9 @@ void launch_stress(hipStream_t s, int G, int n_chunks, const int2* chunks, const
 }
 
 void launch_edge_vjp(hipStream_t s, int E, const float* pos, const int* snd, const int* rcv, const double4* shift,
-                     const float* dYp, int n_part, float4* g) {
+                     const GradRows& rows, float4* g) {
   if (E <= 0) return;
-  edge_vjp_kernel<<<(E + 255) / 256, 256, 0, s>>>(E, pos, snd, rcv, shift, dYp, n_part, g);
+  edge_vjp_kernel<<<(E + 255) / 256, 256, 0, s>>>(E, pos, snd, rcv, shift, rows, g);
 }
 
 void launch_forces(hipStream_t s, int N, const int* rcv_off, const int* snd_off, const int* snd_perm,

@@ -502,10 +502,17 @@ constexpr int kStressChunk = 8192;
 void launch_stress(hipStream_t s, int G, int n_chunks, const int2* chunks, const int* chunk_off, const float* pos,
                    const int* snd, const int* rcv, const double4* shift, const float4* g, const double* inv_vol,
                    double* part, double* stress);
-// g from the edges' gradient rows dYp[part][E][16] (dE/dr in element 0, dE/dY
-// in 1..15), summed over the n_part partials in order
+// The edges' gradient rows: n partials [E][16] (dE/dr in element 0, dE/dY in
+// 1..15), `parts` consecutive ones per layer (fewer for the layer that ends the
+// list), each layer's `step` floats below the one before it.
+struct GradRows {
+  const float* first;
+  int64_t step;
+  int parts, n;
+};
+// g from the gradient rows, summed in order
 void launch_edge_vjp(hipStream_t s, int E, const float* pos, const int* snd, const int* rcv, const double4* shift,
-                     const float* dYp, int n_part, float4* g);
+                     const GradRows& rows, float4* g);
 // Edge-product launchers: radial 0 FP32, 1 BF16, 3 split BF16 (FP32-accurate);
 // in 1 and 3 a3 (and t3) point at the three bfloat16 parts [E][3][64];
 // tp_round 0/1/2 none/bf16/fp16.

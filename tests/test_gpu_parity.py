@@ -67,7 +67,7 @@ def test_many_layers_fp32():
     edge prologue (geometry plus the radial hidden layers) takes, so the
     chunked launches are exercised; five linear readouts below the last layer,
     more than one readout launch takes, so the node energies are built over two
-    launches; the backward accumulates dE/dY and dE/de over six layers."""
+    launches; the geometry backward sums dE/dr and dE/dY over six layers."""
     params = model_params(0, K=32, hidden_lmax=1, n_layers=6, **STRESS)
     bo = oracle_blob(params, 5, STRESS_GAINS)
     bl = lib_blob(params, 5, STRESS_GAINS)

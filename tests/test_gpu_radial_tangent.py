@@ -74,3 +74,19 @@ def test_many_edges_match_oracle(nb):
             assert_parity(part, ref, B.MACE_FP32, f"copy {q} nb={nb}")
         assert np.allclose(energy["eps"][n * q:n * (q + 1)], part["eps"], rtol=1e-5, atol=1e-5 * np.abs(ref["eps"]).mean())
         assert np.linalg.norm(part["forces"] - ref["forces"]) <= 1e-5 * np.linalg.norm(ref["forces"])
+
+
+@pytest.mark.parametrize("K,layers,form", [(128, 3, "EDGE"), (128, 8, "FACTORED"), (64, 5, "EDGE")])
+def test_gradient_rows_of_many_layers_match_fp64(K, layers, form):
+    """A layer's gradient rows take the hidden radial outputs of the layer above
+    (both of them at K = 128), which the next call writes again: several calls.
+    (Plain weights and a c_norm of the mean degree: each layer is cubic in its
+    input, and eight of them with the gains of the other tests leave FP32.)"""
+    params = model_params(4, K=K, hidden_lmax=1, n_layers=layers, n_species=3, c_norm=20.0)
+    sysm, blob = _blobs(), lib_blob(params, 9)
+    ref = run_gpu(params, sysm, blob, B.MACE_FP64)
+    for radial in (B.MACE_PRODUCTS_SPLIT_BF16, B.MACE_PRODUCTS_FP32):
+        outs = run_gpu(params, sysm, blob, l0_form=getattr(B, "MACE_L0_" + form), radial=radial, repeats=3)
+        assert_parity(outs[0], ref, B.MACE_FP32, f"rows K={K} layers={layers} {form} radial={radial}")
+        for o in outs[1:]:
+            assert np.array_equal(o["forces"], outs[0]["forces"])

@@ -213,3 +213,16 @@ def test_workspace_of_small_graphs_is_the_modes_own(shape, fp32, fp64):
         assert 0 < B.mace_workspace_bytes(desc, N, E, 1, prec) <= bound
     weights = B.mace_weight_layout(desc)[1] + 4 * S * K * K + (4 * S * 64 * S * K if S <= 4 else 0)
     assert 0 < B.mace_workspace_bytes(desc, N, E, 1, B.MACE_FP32) <= fp32 + 12 * weights
+
+
+@pytest.mark.parametrize("shape,bound", [
+    ((2, 128, 2, 2, 36864, 3176252), 33837012224), ((2, 128, 5, 0, 1536, 82900), 722965760),
+    ((2, 128, 5, 0, 36864, 3176252), 24662737408), ((2, 128, 8, 0, 36864, 3176252), 31788838656),
+    ((4, 96, 3, (2, 1), 36864, 3176252), 29734039296), ((10, 64, 8, 2, 36864, 3176252), 33211590144)])
+def test_workspace_of_large_graphs(shape, bound):
+    """What a graph of many edges takes, with any number of layers: no more than
+    with one set of gradient partials reused by every layer (bound)."""
+    S, K, T, hl, N, E = shape
+    desc = B.make_desc(n_species=S, K=K, hidden_lmax=hl, r_cut=5.0, c_norm=1.0, n_layers=T)
+    for prec in (B.MACE_FP32, B.MACE_BF16_LINEAR, B.MACE_FP16_LINEAR, B.MACE_BF16_RADIAL):
+        assert 0 < B.mace_workspace_bytes(desc, N, E, 1, prec) <= bound
