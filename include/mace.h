@@ -292,7 +292,9 @@ const char* mace_status_string(mace_status s);
  * between reads).  mace_profile_read waits for those events and returns the
  * summed kernel milliseconds and the launch count since the last select or
  * read; MACE_ENOSPACE if launches were dropped.  mace_kernel_name gives the
- * class's kernel symbol stem ("" when out of range). */
+ * class's kernel symbol stem ("" when out of range).  The class linear_kernel
+ * holds every channel-mixing linear, linear_split_kernel those of them that
+ * ran on split-BF16 products. */
 mace_status mace_profile_select(mace_graph* g, int32_t kernel);
 mace_status mace_profile_read(mace_graph* g, double* total_ms, int64_t* launches);
 const char* mace_kernel_name(int32_t kernel);

@@ -353,13 +353,15 @@ void carve64(const Model& m, int64_t N, int64_t E, Carver& c, Buffers64& b) {
 enum KernelId {
   KID_EDGE_FEATURES = 0, KID_TP_FWD, KID_LINEAR, KID_SYMCON_FWD, KID_READOUT,
   KID_TP_BWD, KID_SYMCON_BWD, KID_SENDER_SUM, KID_EDGE_BWD, KID_FORCES, KID_GRAPH_ENERGY,
-  KID_L0_GATHER, KID_L0_BWD, KID_COUNT
+  KID_L0_GATHER, KID_L0_BWD,
+  KID_LINEAR_SPLIT,   // those of KID_LINEAR's launches that take split products
+  KID_COUNT
 };
 const char* kKernelNames[KID_COUNT] = {
   "edge_prologue_kernel", "tpr_fwd_kernel", "linear_kernel", "symcon_fwd_kernel",
   "readout_kernel", "tpr_bwd_kernel", "symcon_bwd_kernel", "sender_sum_kernel",
   "edge_vjp_kernel", "forces_kernel", "graph_energy_kernel", "l0_gather_kernel",
-  "l0_edge_bwd_kernel"};
+  "l0_edge_bwd_kernel", "linear_split_kernel"};
 constexpr int kProfPairs = 4096;
 
 struct mace_graph {
@@ -447,10 +449,12 @@ bool launchable(const mace_graph* h) {
   return true;
 }
 
-// A linear launch, bracketed for profiling; while the linear class is
-// selected its algorithmic work is summed too.
+// A linear launch, bracketed for profiling (in its class, and where it takes
+// split products in that class); while the linear class is selected its
+// algorithmic work is summed too.
 void run_linear(mace_graph* h, hipStream_t s, const LinPlanRef& P, const LinArgs& a) {
-  ProfScope ps(h, KID_LINEAR, s);
+  const bool split_class = h->prof_kernel == KID_LINEAR_SPLIT && linear_takes_split(P, a);
+  ProfScope ps(h, split_class ? KID_LINEAR_SPLIT : KID_LINEAR, s);
   if (ps.on && a.n_quads > 0 && P.host.plan.n_groups > 0) {
     double f = 0.0, b = 0.0;
     linear_work(P.host.plan, a, h->N, h->m.d.n_species, &f, &b);

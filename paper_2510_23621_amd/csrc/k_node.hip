@@ -353,11 +353,16 @@ linear_split_kernel(const LinLaunch* __restrict__ Lp, LinArgs a, int KI) {
   }
 }
 
-bool launch_linear_split(hipStream_t s, const LinPlanRef& P, const LinArgs& a, int KI) {
-  const int64_t qc = (int64_t)a.n_quads * P.host.n_gc;
-  // columns per block: all K up to 128, two halves of a factorised first layer's 192 or 256
-  const int nz = a.K > 128 ? 2 : 1, ncg = a.K / 32 / nz;
-  if (qc * nz < kLinSplitMinGrid) return false;
+// column blocks of a split launch: a block takes all K columns up to 128, half
+// of a factorised first layer's 192 or 256
+int split_col_blocks(const LinArgs& a) { return a.K > 128 ? 2 : 1; }
+
+bool linear_takes_split(const LinPlanRef& P, const LinArgs& a) {
+  return a.wsp && (int64_t)a.n_quads * P.host.n_gc * split_col_blocks(a) >= kLinSplitMinGrid;
+}
+
+void launch_linear_split(hipStream_t s, const LinPlanRef& P, const LinArgs& a, int KI) {
+  const int nz = split_col_blocks(a), ncg = a.K / 32 / nz;
   const dim3 grid(a.n_quads, P.host.n_gc, nz);
   switch (ncg) {
     case 1: linear_split_kernel<1><<<grid, 256, 0, s>>>(P.dev, a, KI); break;
@@ -365,7 +370,6 @@ bool launch_linear_split(hipStream_t s, const LinPlanRef& P, const LinArgs& a, i
     case 3: linear_split_kernel<3><<<grid, 192, 0, s>>>(P.dev, a, KI); break;
     case 4: linear_split_kernel<4><<<grid, 256, 0, s>>>(P.dev, a, KI); break;
   }
-  return true;
 }
 
 // The split packed copy of nb consecutive KI x K blocks (row-major [in][out]) of
@@ -572,7 +576,10 @@ void launch_linear(hipStream_t s, const LinPlanRef& P, const LinArgs& a) {
   const int halves = (a.K / 16 + kLinCt - 1) / kLinCt;
   dim3 grid(a.n_quads, P.host.n_gc, halves), block(64 * kLinQuad);
   const int KI0 = a.KI > 0 ? a.KI : a.K;
-  if (a.wsp && launch_linear_split(s, P, a, KI0)) return;
+  if (linear_takes_split(P, a)) {
+    launch_linear_split(s, P, a, KI0);
+    return;
+  }
   if (a.K == 128 && KI0 <= 128 && (int64_t)a.n_quads * P.host.n_gc >= kLinWideGrid) {
     // wide blocks: all 128 output columns, each input row read once
     dim3 gw(a.n_quads, P.host.n_gc, 1);

@@ -584,6 +584,8 @@ void launch_symcon_fwd(hipStream_t s, int lout_max, int N, int K, const int* spe
 void launch_symcon_bwd(hipStream_t s, int lout_max, int N, int K, const int* species, const float* A,
                        SymW w, const float* dB, float* dA, int rnd);
 void launch_linear(hipStream_t s, const LinPlanRef& plan, const LinArgs& a);
+// whether launch_linear takes split-BF16 products for this launch
+bool linear_takes_split(const LinPlanRef& plan, const LinArgs& a);
 void launch_pack_split(hipStream_t s, int KI, int K, int64_t blocks, int64_t part, const float* src,
                        unsigned short* dst);
 // Algorithmic work of one linear launch over N nodes: flops = 2 K^2 per

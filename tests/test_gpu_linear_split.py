@@ -2,7 +2,8 @@
 against the FP64 mode: every column split of a block (K = 32 to 128 and the
 factorised first layer's contraction widths 64 S = 64 to 256 in both
 directions), several species with partly filled tiles and quads, and launches
-of few components that only large graphs send there."""
+of few components that only large graphs send there. Which launches took them
+is read from the library's launch counts."""
 import numpy as np
 import pytest
 import torch
@@ -13,6 +14,7 @@ from synth.configs import model_params
 pytestmark = pytest.mark.gpu
 
 B = pytest.importorskip("paper_2510_23621_amd.binding")
+from paper_2510_23621_amd.graph import MaceGraph  # noqa: E402
 from gpu_common import STRESS, STRESS_GAINS, assert_parity, lib_blob, run_gpu  # noqa: E402
 
 
@@ -32,15 +34,39 @@ def _clusters(n, species):
     return synth.System(pos, rng.integers(0, species, n).astype(np.int32), None, gid, int(gid[-1]) + 1)
 
 
-@pytest.mark.parametrize("K,hl,S,n", [(32, 2, 1, 1025), (64, 1, 2, 1207), (96, 1, 3, 1300), (128, 2, 4, 1100),
-                                      (128, 1, 5, 1331), (96, 2, 6, 1400), (32, 1, 2, 4133)])
-def test_split_linears_match_fp64(K, hl, S, n):
+def _linear_launches(params, sysm, blob, form, products):
+    """(launches of the channel-mixing linears, those on split products) in one
+    forces call."""
+    snd, rcv, _ = B.mace_neighbor_list(sysm.positions, params["r_cut"], None, sysm.graph_of_atom, sysm.n_graphs)
+    g = MaceGraph(B.make_desc(**params), blob, sysm.species, np.stack([snd, rcv]), None, None, sysm.graph_of_atom,
+                  sysm.n_graphs, B.MACE_FP32)
+    B.mace_layer0_form(g.handle, form)
+    B.mace_fp32_products(g.handle, products)
+    pos = torch.from_numpy(sysm.positions.astype(np.float32)).cuda()
+    counts = []
+    for name in ("linear_kernel", "linear_split_kernel"):
+        B.mace_profile_select(g.handle, B.kernel_ids()[name])
+        g.energy_forces(pos)
+        counts.append(B.mace_profile_read(g.handle)[1])
+    g.close()
+    return counts
+
+
+# n_split: of the ten launches of a forces call, those with 256 blocks or more:
+# the 16 and more components of the first layer and of the mid arrays always
+# (twice each way), the 1 to 9 of the hidden features in the largest graph
+@pytest.mark.parametrize("K,hl,S,n,n_split", [(32, 2, 1, 1025, 4), (64, 1, 2, 1207, 4), (96, 1, 3, 1300, 4),
+                                              (128, 2, 4, 1100, 4), (128, 1, 5, 1331, 4), (96, 2, 6, 1400, 4),
+                                              (32, 1, 2, 4133, 8)])
+def test_split_linears_match_fp64(K, hl, S, n, n_split):
     params = model_params(4, K=K, hidden_lmax=hl, n_species=S, **STRESS)
     sysm, blob = _clusters(n, S), lib_blob(params, 11, STRESS_GAINS)
     ref = run_gpu(params, sysm, blob, B.MACE_FP64)
     forms = (B.MACE_L0_FACTORED, B.MACE_L0_EDGE) if S <= 4 else (B.MACE_L0_EDGE,)
     for form in forms:
         err = []
+        assert _linear_launches(params, sysm, blob, form, B.MACE_PRODUCTS_SPLIT_BF16) == [10, n_split]
+        assert _linear_launches(params, sysm, blob, form, B.MACE_PRODUCTS_FP32) == [10, 0]
         for products in (B.MACE_PRODUCTS_SPLIT_BF16, B.MACE_PRODUCTS_FP32):
             gpu = run_gpu(params, sysm, blob, l0_form=form, radial=products)
             err.append(assert_parity(gpu, ref, B.MACE_FP32, f"K={K} hl={hl} S={S} n={n} form={form} products={products}"))
