@@ -52,8 +52,7 @@ struct Model {
   int64_t comb_off = 0;    // after the blob: layer-0 path-merging x species weights [4][S][K][K]
   int l0_ki = 0;           // channels of the factorised first layer's U (64 S), 0 when S > kL0MaxSpecies
   int64_t l0_off = 0;      // after those: its weights [4][S][l0_ki][K] (transposed copy [4][S][K][l0_ki])
-  int64_t total_ext = 0;   // blob + combined weights (FP32 copies only)
-  int64_t split_part() const { return (total_ext + 7) / 8 * 8; }   // elements of one part of the split copies
+  int64_t total_ext = 0;   // blob + combined weights (FP32 copies, and one part of the split ones), a multiple of 8
   int64_t w3_total = 0;    // elements of the last radial layers together (layer t's begin at LayerPlan::w3_off)
   int max_P = 0, max_mid = 0, max_din = 0, max_dout = 0;
 };
@@ -152,9 +151,12 @@ mace_status build_model(const mace_model_desc* desc, Model& m) {
     m.layers.push_back(L);
   }
   m.total = o;
-  m.comb_off = o;
+  // the blob's blocks begin at multiples of 8 floats (its one tensor of another
+  // size is the last), and those after it have to: their packed copies are read
+  // in pieces of 8
+  m.comb_off = (o + 7) / 8 * 8;
   m.l0_ki = S <= kL0MaxSpecies ? 64 * (int)S : 0;
-  m.l0_off = o + 4 * S * K * K;
+  m.l0_off = m.comb_off + 4 * S * K * K;
   m.total_ext = m.l0_off + 4 * S * (int64_t)m.l0_ki * K;
   return MACE_OK;
 }
@@ -229,8 +231,8 @@ void carve(const Model& m, int64_t N, int64_t E, int G, mace_precision prec, Car
     b.wbfT = c.take<unsigned short>(m.total);
   }
   if (prec == MACE_FP32) {
-    b.wsp = c.take<unsigned short>(3 * m.split_part());
-    b.wspT = c.take<unsigned short>(3 * m.split_part());
+    b.wsp = c.take<unsigned short>(3 * m.total_ext);
+    b.wspT = c.take<unsigned short>(3 * m.total_ext);
   }
   if (prec != MACE_FP64) b.wrad = c.take<unsigned short>(3 * kRadPart * T);
   b.sp_table = c.take<float>(S * K);
@@ -686,10 +688,9 @@ LinArgs largs(mace_graph* h, const float* x, float* y, const float* residual, bo
   a.w = transposed ? h->b.wT : h->b.w;
   a.wt = transposed ? h->b.w : h->b.wT;
   a.wbf = transposed ? h->b.wbfT : h->b.wbf;
-  // split products in the FP32 mode (the packed blocks are read in 16-byte pieces)
-  const bool split = h->prec == MACE_FP32 && h->radial_split && h->m.comb_off % 8 == 0;
+  const bool split = h->prec == MACE_FP32 && h->radial_split;   // split products in the FP32 mode
   a.wsp = split ? (transposed ? h->b.wspT : h->b.wsp) : nullptr;
-  a.wsp_part = h->m.split_part();
+  a.wsp_part = h->m.total_ext;
   a.quad_node = h->b.quad_node;
   a.quad_species = h->b.quad_species;
   a.n_quads = h->n_quads;
@@ -1486,8 +1487,8 @@ mace_status mace_graph_setup(const mace_model_desc* desc, const float* weights, 
     // the same of every K x K block, of the composed layer-0 weights and of the
     // factorised first layer's, and of their transposes
     auto pack = [&](int KI, int KO, int64_t blocks, int64_t off) {
-      launch_pack_split(s, KI, KO, blocks, m.split_part(), b.w + off, b.wsp + off);
-      launch_pack_split(s, KO, KI, blocks, m.split_part(), b.wT + off, b.wspT + off);
+      launch_pack_split(s, KI, KO, blocks, m.total_ext, b.w + off, b.wsp + off);
+      launch_pack_split(s, KO, KI, blocks, m.total_ext, b.wT + off, b.wspT + off);
     };
     for (auto& t : m.tensors)
       if (t.shape.size() >= 2 && t.shape[t.shape.size() - 1] == K && t.shape[t.shape.size() - 2] == K)

@@ -55,11 +55,13 @@ def _linear_launches(params, sysm, blob, form, products):
 # n_split: of the ten launches of a forces call, those with 256 blocks or more:
 # the 16 and more components of the first layer and of the mid arrays always
 # (twice each way), the 1 to 9 of the hidden features in the largest graph
-@pytest.mark.parametrize("K,hl,S,n,n_split", [(32, 2, 1, 1025, 4), (64, 1, 2, 1207, 4), (96, 1, 3, 1300, 4),
-                                              (128, 2, 4, 1100, 4), (128, 1, 5, 1331, 4), (96, 2, 6, 1400, 4),
-                                              (32, 1, 2, 4133, 8)])
-def test_split_linears_match_fp64(K, hl, S, n, n_split):
-    params = model_params(4, K=K, hidden_lmax=hl, n_species=S, **STRESS)
+# (rh: the width of the last readout, after which the composed weights begin)
+@pytest.mark.parametrize("K,hl,S,n,n_split,rh", [(32, 2, 1, 1025, 4, 16), (64, 1, 2, 1207, 4, 16),
+                                                 (96, 1, 3, 1300, 4, 16), (128, 2, 4, 1100, 4, 16),
+                                                 (128, 1, 5, 1331, 4, 16), (96, 2, 6, 1400, 4, 16),
+                                                 (32, 1, 2, 4133, 8, 16), (64, 1, 3, 1100, 4, 5), (96, 2, 5, 1300, 4, 1)])
+def test_split_linears_match_fp64(K, hl, S, n, n_split, rh):
+    params = model_params(4, K=K, hidden_lmax=hl, n_species=S, readout_hidden=rh, **STRESS)
     sysm, blob = _clusters(n, S), lib_blob(params, 11, STRESS_GAINS)
     ref = run_gpu(params, sysm, blob, B.MACE_FP64)
     forms = (B.MACE_L0_FACTORED, B.MACE_L0_EDGE) if S <= 4 else (B.MACE_L0_EDGE,)
@@ -69,7 +71,7 @@ def test_split_linears_match_fp64(K, hl, S, n, n_split):
         assert _linear_launches(params, sysm, blob, form, B.MACE_PRODUCTS_FP32) == [10, 0]
         for products in (B.MACE_PRODUCTS_SPLIT_BF16, B.MACE_PRODUCTS_FP32):
             gpu = run_gpu(params, sysm, blob, l0_form=form, radial=products)
-            err.append(assert_parity(gpu, ref, B.MACE_FP32, f"K={K} hl={hl} S={S} n={n} form={form} products={products}"))
+            err.append(assert_parity(gpu, ref, B.MACE_FP32, f"K={K} hl={hl} S={S} n={n} rh={rh} form={form} products={products}"))
         # no less accurate than FP32 products: both are within a few roundoffs of
         # the exact result, and a dropped part (2^-16) would show as 100 times more
         assert err[0]["forces"] <= 2 * err[1]["forces"] + 1e-7
