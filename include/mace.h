@@ -48,7 +48,9 @@ typedef enum {
                              MLP (the P*K-wide one) on BF16 operands with FP32
                              accumulation: R = bf16(a3) bf16(W) forward, and
                              backward dE/dr = sum dE/dR dR/dr with dR/dr =
-                             (da3/dr to 16 significand bits) bf16(W) */
+                             da3/dr bf16(W), da3/dr to 16 significand bits in
+                             the layers in per-edge form and in FP32 in a
+                             factorised first layer */
   MACE_FP64 = 4           /* debug precision: every step in FP64 on the vector
                              units (plain kernels, not tuned for speed), every
                              layer in per-edge form; positions, node energies
@@ -125,8 +127,8 @@ mace_status mace_neighbor_list(int64_t n_atoms, const double* positions, const d
  * Outputs (dev) of capacity max_edges: sender [E], receiver [E], shifts
  * [E][3], sorted by (receiver, sender, S).  workspace (dev) of at least
  * mace_neighbor_workspace_bytes.  Waits for the stream once, to read the
- * edge count into *n_edges (host); the outputs are then written by work
- * enqueued on stream.  MACE_ENOSPACE (with *n_edges = the count, outputs
+ * edge count into *n_edges (host); the outputs have been written when it
+ * returns.  MACE_ENOSPACE (with *n_edges = the count, outputs
  * untouched) when max_edges is too small; MACE_ENONFINITE / MACE_ERANGE for
  * non-finite / out-of-bound coordinates; MACE_EUNSUPPORTED beyond 2^30
  * periodic-image candidates. */
@@ -231,14 +233,21 @@ mace_status mace_layer0_form(mace_graph* g, int32_t request, int32_t* in_use);
 
 /* Operands of the P*K-wide last radial layer (formed inside the edge-product
  * kernels of the layers in per-edge form) in the modes other than
- * MACE_BF16_RADIAL, and in MACE_FP32 of the channel-mixing linears too.
+ * MACE_BF16_RADIAL, and in MACE_FP32 of the channel-mixing linears too (split
+ * products there in launches of at least 256 blocks, one block being up to 64
+ * atoms of one species and one component; smaller launches stay on FP32 MFMA,
+ * which is faster for them).
  *   MACE_PRODUCTS_FP32:       FP32 MFMA (v_mfma_f32_16x16x4_f32);
  *   MACE_PRODUCTS_SPLIT_BF16: every FP32 operand x carried as x0 + x1 + x2,
  *     the bfloat16 roundings of x, x - x0 and x - x0 - x1 (together exact),
  *     and each product formed from the six partial products down to
  *     relative size 2^-18 on BF16 MFMA with FP32 accumulation: as accurate
  *     as FP32 products (the dropped terms are below 2^-26 relative), at a
- *     fraction of the FP32 MFMA time.  The default.
+ *     fraction of the FP32 MFMA time.  The default.  Range: as FP32 for
+ *     operands of magnitude 2e-31 to 3.38e38 and zero.  Below, the lower parts
+ *     leave the range of normal numbers (an error of up to 1.2e-38 in the
+ *     operand); above, the first part rounds to infinity; and an infinite
+ *     operand gives NaN where an FP32 product gives infinity.
  * request < 0 only queries; *in_use (host, may be NULL) receives the setting
  * (MACE_BF16_RADIAL handles report 1 and refuse a change with MACE_EINVAL).
  * Takes effect for calls enqueued after it returns; no device work. */

@@ -76,3 +76,16 @@ def test_split_linears_match_fp64(K, hl, S, n, n_split, rh):
         # the exact result, and a dropped part (2^-16) would show as 100 times more
         assert err[0]["forces"] <= 2 * err[1]["forces"] + 1e-7
         assert err[0]["eps_l2"] <= 2 * err[1]["eps_l2"] + 1e-7
+
+
+@pytest.mark.parametrize("power", [-90, -60, 0])
+def test_split_linears_of_small_features_match_fp64(power):
+    """Features of 2^power times their usual size (the embedding scaled): at
+    2^-90, about 1e-27, the third parts are near 1e-32, in the normal range."""
+    params = model_params(4, K=64, hidden_lmax=1, n_species=2, **STRESS)
+    sysm, blob = _clusters(1207, 2), lib_blob(params, 11, STRESS_GAINS)
+    assert B.mace_weight_layout(B.make_desc(**params))[0][0][:2] == ("embed", 2 * 64)
+    blob[:2 * 64] *= np.float32(2.0 ** power)
+    ref = run_gpu(params, sysm, blob, B.MACE_FP64)
+    gpu = run_gpu(params, sysm, blob)
+    assert_parity(gpu, ref, B.MACE_FP32, f"features times 2^{power}")
