@@ -1228,17 +1228,10 @@ mace_status mace_graph_setup(const mace_model_desc* desc, const float* weights, 
       tspec.push_back(z);
     }
   }
-  // transposed copy of every K x K block (backward linears) and of the last
-  // radial layer [64][P*K] -> [P*K][64] (radial-MLP backward)
+  // transposed copy of every K x K block (backward linears)
   std::vector<float> hwT(hw);
   for (auto& t : m.tensors) {
     const auto& sh = t.shape;
-    if (t.name.size() > 9 && t.name.compare(t.name.size() - 9, 9, ".radial.3") == 0) {
-      const int64_t rows = sh[0], cols = sh[1];
-      for (int64_t r = 0; r < rows; ++r)
-        for (int64_t c2 = 0; c2 < cols; ++c2) hwT[t.offset + c2 * rows + r] = hw[t.offset + r * cols + c2];
-      continue;
-    }
     if (sh.size() >= 2 && sh[sh.size() - 1] == K && sh[sh.size() - 2] == K) {
       int64_t blocks = t.size() / (K * K);
       for (int64_t q = 0; q < blocks; ++q) {

@@ -11,10 +11,11 @@
 // order) in tiles of 16. For each tile the forward forms R
 // with FP32 MFMA (v_mfma_f32_16x16x4_f32; lane l supplies A[l%16][l/16] and
 // B[l/16][l%16], result register r holds D[4(l/16)+r][l%16]): rows are the
-// tile's edges, columns the wave's channels. Lane l therefore holds R for
-// channel l%16 and the four edges 4(l/16)..4(l/16)+3, and contracts exactly
-// those edges; the four lane groups are summed by a fixed butterfly at the
-// end of the receiver, so the result does not depend on scheduling.
+// tile's edges in transposed order, columns the wave's channels. Lane l
+// therefore holds R for channel l%16 and the four edges e0 + 4 q + l/16,
+// q = 0..3, and contracts exactly those edges; the four lane groups are summed
+// by a fixed butterfly at the end of the receiver, so the result does not
+// depend on scheduling.
 //
 // A block is a few waves on as many receivers, sharing one channel tile; the
 // tile's slice of W3 (64 x P x 16 floats) sits in LDS for the block's life,
@@ -89,23 +90,21 @@ __device__ __forceinline__ void load_w3_slice(const float* __restrict__ W3, int 
   });
 }
 
-// MFMA row of the tile that carries edge e0 + rho: rho itself, or with TRP the
-// transposed order 4 (rho % 4) + rho / 4, which puts edge e0 + 4 q + (l/16) in
-// result register q of lane l (a tile of n edges then needs ceil(n / 4) edge
-// iterations per lane instead of min(n, 4)).
-template <bool TRP>
-__device__ __forceinline__ int tile_edge(int rho) { return TRP ? 4 * (rho & 3) + (rho >> 2) : rho; }
+// Edge (from e0) that MFMA row rho of a tile carries: the transposed order
+// 4 (rho % 4) + rho / 4 puts edge e0 + 4 q + (l/16) in result register q of lane
+// l, so that a tile of n edges needs ceil(n / 4) edge iterations per lane, where
+// the order of the rows would need min(n, 4).
+__device__ __forceinline__ int tile_edge(int rho) { return 4 * (rho & 3) + (rho >> 2); }
 
 // R of the 16 edges e0 .. e0+15 (edges at or past e_end get R = 0) for the
-// wave's channel tile: r[p][q] = R[e0 + 4(l/16) + q][p][16 ct + l%16]
-// (R[e0 + 4 q + l/16] with TRP).
+// wave's channel tile: r[p][q] = R[e0 + 4 q + l/16][p][16 ct + l%16].
 // The 64-long reduction runs in the order j = 16 qq + 4 s + c so that every
 // lane reads its A operand as four float4.
-template <int P, bool TRP = false>
+template <int P>
 __device__ __forceinline__ void tile_radial(const float* __restrict__ a3, int e0, int e_end,
                                             const float* __restrict__ sW, f4* r) {
   const int l = threadIdx.x & 63;
-  const int row = e0 + tile_edge<TRP>(l & 15);
+  const int row = e0 + tile_edge(l & 15);
   const float keep = row < e_end ? 1.f : 0.f;
   const f4* arow = reinterpret_cast<const f4*>(a3 + (size_t)min(row, e_end - 1) * 64 + 4 * (l >> 4));
   f4 a[4];
@@ -155,11 +154,11 @@ __device__ __forceinline__ void load_w3_slice_bf16(const float* __restrict__ W3,
 // operands are read kBf16Ahead paths ahead of their MFMAs, so that the LDS
 // reads do not stall each path's pair of products.
 constexpr int kBf16Ahead = 4;
-template <int P, bool TRP = false>
+template <int P>
 __device__ __forceinline__ void tile_radial_bf16(const unsigned short* __restrict__ a3x, int e0, int e_end,
                                                  const unsigned short* __restrict__ sWb, f4* r) {
   const int l = threadIdx.x & 63;
-  const int row = e0 + tile_edge<TRP>(l & 15);
+  const int row = e0 + tile_edge(l & 15);
   const unsigned short* arow = a3x + (size_t)min(row, e_end - 1) * 192 + 8 * (l >> 4);
   const unsigned short* wb = sWb + (l & 15) * kWbPitch + 8 * (l >> 4);
   constexpr int D = kBf16Ahead < P ? kBf16Ahead : P;
@@ -230,12 +229,12 @@ __device__ __forceinline__ void load_w3_slice_x3(const float* __restrict__ W3, i
 }
 
 // tile_radial_x3 below l = 2 (described there)
-template <int P, bool TRP = false>
+template <int P>
 __device__ __forceinline__ void tile_radial_x3_chain(const unsigned short* __restrict__ a3x, int e0, int e_end,
                                                      const unsigned short* __restrict__ sWx, f4* r) {
   constexpr int part = P * 16 * kWbPitch;
   const int l = threadIdx.x & 63;
-  const int row = e0 + tile_edge<TRP>(l & 15);
+  const int row = e0 + tile_edge(l & 15);
   const int crow = min(row, e_end - 1);
   const unsigned short* wb = sWx + (l & 15) * kWbPitch + 8 * (l >> 4);
 #pragma unroll
@@ -272,16 +271,16 @@ __device__ __forceinline__ void tile_radial_x3_chain(const unsigned short* __res
 // of six products at a time, only one K step's A parts live; at l = 2 (P = 17,
 // two waves per SIMD) both K steps' A parts are loaded first and the paths go
 // in pairs (below).
-template <int P, bool TRP = false>
+template <int P>
 __device__ __forceinline__ void tile_radial_x3(const unsigned short* __restrict__ a3x, int e0, int e_end,
                                                const unsigned short* __restrict__ sWx, f4* r) {
   if constexpr (P <= 10) {
-    tile_radial_x3_chain<P, TRP>(a3x, e0, e_end, sWx, r);
+    tile_radial_x3_chain<P>(a3x, e0, e_end, sWx, r);
     return;
   }
   constexpr int part = P * 16 * kWbPitch;
   const int l = threadIdx.x & 63;
-  const int row = e0 + tile_edge<TRP>(l & 15);
+  const int row = e0 + tile_edge(l & 15);
   const int crow = min(row, e_end - 1);
   const unsigned short* wb = sWx + (l & 15) * kWbPitch + 8 * (l >> 4);
 #pragma unroll
@@ -341,8 +340,6 @@ __device__ __forceinline__ void tile_radial_x3(const unsigned short* __restrict_
 // j), s(r) = (r >> 1) & 7.
 __device__ __forceinline__ int swz_fwd(int r, int c) { return r * 64 + 8 * (c ^ ((r >> 1) & 7)); }
 
-// Y rows of the wave's 16-edge tile into LDS: sy[row][m], row pitch kYPitch.
-// Lane l moves float4 number l%4 of row l/4.
 // The precision study's operand rounding of the edge product (rnd: 0 none,
 // 1 bfloat16, 2 binary16, round to nearest even) of the radial weights of a
 // tile; the harmonics and the sender features arrive rounded (the host runtime
@@ -362,6 +359,8 @@ __device__ __forceinline__ void round_tile(f4* r, int rnd) {
   }
 }
 
+// Y rows of the wave's 16-edge tile into LDS: sy[row][m], row pitch kYPitch.
+// Lane l moves float4 number l%4 of row l/4.
 __device__ __forceinline__ void stage_y(const float* __restrict__ Y, int e0, int e_end, float* sy) {
   const int l = threadIdx.x & 63;
   const int row = l >> 2, ch = l & 3;
@@ -444,9 +443,9 @@ tpr_fwd_kernel(
       }
       stage_y(Y, e0, e_end, sy);
       f4 r[P];
-      if constexpr (RM == 1) tile_radial_bf16<P, true>(a3x, e0, e_end, reinterpret_cast<const unsigned short*>(sW), r);
-      else if constexpr (SPLIT) tile_radial_x3<P, true>(a3x, e0, e_end, reinterpret_cast<const unsigned short*>(sW), r);
-      else tile_radial<P, true>(a3, e0, e_end, sW, r);
+      if constexpr (RM == 1) tile_radial_bf16<P>(a3x, e0, e_end, reinterpret_cast<const unsigned short*>(sW), r);
+      else if constexpr (SPLIT) tile_radial_x3<P>(a3x, e0, e_end, reinterpret_cast<const unsigned short*>(sW), r);
+      else tile_radial<P>(a3, e0, e_end, sW, r);
       round_tile<P>(r, rnd);
       // a tile of n edges fills registers q < ceil(n / 4) (edges past e_end
       // carry R = 0); the scheduling barrier keeps one edge's operands live at
@@ -593,13 +592,8 @@ __device__ __forceinline__ void load_w3_bwd(const float* __restrict__ W3, int K,
   }
 }
 
-#ifndef V_RR
-#define V_RR 3
-#define V_RG 4
-#define V_PRIO 1
-#endif
-constexpr int kRingR = V_RR;    // W3 operand sets in flight in the radial products
-constexpr int kRingG = 4;    // G-table entries in flight (one coupling pair each)
+constexpr int kRingR = 3;   // W3 operand sets in flight in the radial products
+constexpr int kRingG = 4;   // G-table entries in flight (one coupling pair each)
 
 // R and R' of the paths PA .. PB - 1 in the edge-lane layout. RM 3: six partial
 // products per operand pair, the smallest first. RM 1: bf16(a3) bf16(W3) for R,
