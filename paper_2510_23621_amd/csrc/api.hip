@@ -1714,11 +1714,12 @@ mace_status mace_debug_edge_features(int64_t n, const float* vec, double r_cut, 
     double dx = vec[3 * e], dy = vec[3 * e + 1], dz = vec[3 * e + 2];
     double rr = sqrt(dx * dx + dy * dy + dz * dz);
     double inv = 1.0 / rr;
-    double y[16], eb[16];
+    double y[16];
+    float eb[16];
     sh16<double>(dx * inv, dy * inv, dz * inv, y);
-    bessel_env<double>(rr, r_cut, envelope_p, n_bessel, eb);
+    bessel_env_dr<16, false>(rr, inv, radial_basis(r_cut, envelope_p, n_bessel), eb, nullptr);
     for (int q = 0; q < 16; ++q) Y[16 * e + q] = (float)y[q];
-    for (int q = 0; q < n_bessel; ++q) rbf[e * n_bessel + q] = (float)eb[q];
+    for (int q = 0; q < n_bessel; ++q) rbf[e * n_bessel + q] = eb[q];
   }
   return MACE_OK;
 }

@@ -333,7 +333,7 @@ edge_prologue_kernel(int E, const float* __restrict__ pos, const int* __restrict
 void launch_edge_prologue(hipStream_t s, int E, const float* pos, const int* snd, const int* rcv,
                           const double4* shift, double rc, int p, int nb, float* Y, const RadialSet& rs, int* status) {
   if (E <= 0) return;
-  const RadialBasis rb{1.0 / rc, 3.14159265358979323846 / rc, std::sqrt(2.0 / rc), p, nb};
+  const RadialBasis rb = radial_basis(rc, p, nb);
   auto go = [&](auto T, auto R) {
     constexpr bool TAN = decltype(T)::value, RND = decltype(R)::value;
     auto run = [&](auto TE, auto ONE) {

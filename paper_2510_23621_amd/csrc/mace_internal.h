@@ -240,12 +240,15 @@ struct RadialBasis {
   double inv_rc, pi_rc, c;   // 1/rc, pi/rc, sqrt(2/rc)
   int p, nb;
 };
+inline RadialBasis radial_basis(double rc, int p, int nb) {
+  return {1.0 / rc, 3.14159265358979323846 / rc, sqrt(2.0 / rc), p, nb};
+}
 
 // As bessel_env (FP64) for a length r with inverse inv, e_1 .. e_NBP (rb.nb <=
 // NBP; the others continue the series), with TAN also the derivatives de_n/dr:
 //   d sin(n theta)/dr = n (pi/rc) cos(n theta), cos(n theta) by the same recurrence.
 template <int NBP, bool TAN>
-__device__ __forceinline__ void bessel_env_dr(double r, double inv, const RadialBasis& rb, float* e, float* de) {
+__host__ __device__ __forceinline__ void bessel_env_dr(double r, double inv, const RadialBasis& rb, float* e, float* de) {
   const double xr = r * rb.inv_rc;
   double q = 0.5 * rb.p * (rb.p + 1), dq = 0.0;   // the polynomial and its derivative in x
   for (int j = rb.p - 2; j >= 0; --j) {

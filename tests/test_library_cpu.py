@@ -226,3 +226,16 @@ def test_workspace_of_large_graphs(shape, bound):
     desc = B.make_desc(n_species=S, K=K, hidden_lmax=hl, r_cut=5.0, c_norm=1.0, n_layers=T)
     for prec in (B.MACE_FP32, B.MACE_BF16_LINEAR, B.MACE_FP16_LINEAR, B.MACE_BF16_RADIAL):
         assert 0 < B.mace_workspace_bytes(desc, N, E, 1, prec) <= bound
+
+
+@pytest.mark.parametrize("p,nb", [(1, 1), (2, 16), (6, 9)])
+def test_radial_basis_of_other_envelopes_and_sizes_matches_oracle(p, nb):
+    """The prologue's radial basis, from short edges to the cutoff and past it."""
+    r = np.concatenate([np.linspace(0.05, 4.9999, 300), [5.0, 5.5, 1e6]]).astype(np.float32)
+    vec = np.zeros((len(r), 3), np.float32)
+    vec[:, 2] = r
+    _, rbf = B.mace_debug_edge_features(vec, 5.0, p, nb)
+    ref = mace.bessel_basis(torch.from_numpy(r.astype(np.float64)), 5.0, nb, p).numpy()
+    assert not rbf[r >= 5.0].any()
+    # FP64 rounded to FP32 once: 2^-24 of the largest value (sin(n theta) near its zeros is absolute)
+    np.testing.assert_allclose(rbf[r < 5.0], ref[r < 5.0], rtol=1e-6, atol=2 ** -24 * np.abs(ref[r < 5.0]).max())
