@@ -30,9 +30,13 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 FP32_MFMA_PEAK_TFLOPS = 157.3
-# FP32 vector arithmetic without packed (two-wide) FP32 instructions, which
-# this build does not emit: 256 CUs x 4 SIMDs x 16 lanes x 2 flop x 2.4 GHz
-FP32_VALU_PEAK_TFLOPS = 78.6
+# a split-BF16 (FP32-accurate) product is six BF16 ones
+SPLIT_PRODUCTS = 6
+# FP32 vector arithmetic: 256 CUs x 4 SIMDs x 32 lanes x 2 flop x 2.4 GHz. Reached
+# without packed (two-wide) instructions, which this build does not emit: with two
+# waves and more a SIMD issues a wave's 64-lane multiply-add every 2.3 to 4.1
+# cycles, by the instruction's form (118 to 72 TFLOP/s measured)
+FP32_VALU_PEAK_TFLOPS = 157.3
 BF16_MFMA_PEAK_TFLOPS = 2500.0
 KERNEL_SOURCES = {"edge_prologue_kernel": "k_radial.hip", "tpr_fwd_kernel": "k_tpr.hip", "tpr_bwd_kernel": "k_tpr.hip", "linear_kernel": "k_node.hip",
                   "l0_gather_kernel": "k_layer0.hip", "l0_edge_bwd_kernel": "k_layer0.hip",
@@ -84,20 +88,22 @@ def edge_product_work(layer, K, E, N, backward):
 
 def hbm_class_bytes(name, model, N, E, l0_factored, n_species, parts):
     """Compulsory bytes of every launch of an HBM-priced kernel class in one
-    step, summed: each input and output the kernel must move, once."""
+    step, summed: each input and output the kernel must move, once. parts:
+    bfloat16 parts of a3 and da3/dr (64 each) that the edge products read per
+    edge, 0 where they read FP32."""
     K, layers = model["K"], model["layers"]
     ki = 64 * n_species
     tot = 0.0
     for t, L in enumerate(layers):
         mid, din = L["mid"], L["din"]
         fact = l0_factored and t == 0
-        a3b = 384 if (parts and not fact) else 256
+        a3b = 128 * parts if (parts and not fact) else 512
         if name == "l0_gather_kernel" and fact:
             tot += E * (256 + 64 + 4) + (N + 1) * 4 + N * 16 * ki * 4
         elif name == "l0_edge_bwd_kernel" and fact:
             tot += N * 16 * ki * 4 + E * (2 * 256 + 64 + 4) + E * 64
         elif name == "edge_prologue_kernel":
-            tot += E * ((12 + 8 + 32 + 64) if t == 0 else 0) + E * 2 * a3b
+            tot += E * ((12 + 8 + 32 + 64) if t == 0 else 0) + E * a3b
         elif name == "sender_sum_kernel" and t > 0:
             tot += E * (din * K * 4 + 4) + N * din * K * 4
     return tot
@@ -201,6 +207,8 @@ class Arm:
         B = self.B
         best, best_ms = None, -1.0
         for name, kid in B.kernel_ids().items():
+            if name == "linear_split_kernel":   # some of linear_kernel's launches
+                continue
             B.mace_profile_select(self.g.handle, kid)
             self.step()
             ms, _ = B.mace_profile_read(self.g.handle)
@@ -213,7 +221,8 @@ class Arm:
         """The channel-mixing linears (every linear_kernel launch of a step):
         algorithmic flops and bytes (summed by the library from the launch
         plans) over their HIP-event time, against the MFMA peak of the mode's
-        operand type and against HBM bandwidth."""
+        products (a sixth of the BF16 peak for split ones; small launches take
+        FP32 MFMA instead) and against HBM bandwidth."""
         B = self.B
         B.mace_profile_select(self.g.handle, B.kernel_ids()["linear_kernel"])
         for _ in range(steps):
@@ -221,7 +230,10 @@ class Arm:
         ms, launches = B.mace_profile_read(self.g.handle)
         flops, byts = B.mace_profile_work(self.g.handle)
         B.mace_profile_select(self.g.handle, -1)
-        peak = FP32_MFMA_PEAK_TFLOPS if self.prec == B.MACE_FP32 else BF16_MFMA_PEAK_TFLOPS
+        peak = BF16_MFMA_PEAK_TFLOPS
+        if self.prec == B.MACE_FP32:
+            peak = (FP32_MFMA_PEAK_TFLOPS if B.mace_fp32_products(self.g.handle, -1) == B.MACE_PRODUCTS_FP32
+                    else BF16_MFMA_PEAK_TFLOPS / SPLIT_PRODUCTS)
         tfl = flops / (ms * 1e-3) / 1e12
         gbs = byts / (ms * 1e-3) / 1e9
         return {"launches_per_step": launches / steps, "avg_launch_ms": round(ms / max(launches, 1), 5),
@@ -235,7 +247,8 @@ class Arm:
         B = self.B
         model = layer_shapes(self.params)
         l0_factored = B.mace_layer0_form(self.g.handle, -1) == B.MACE_L0_FACTORED
-        parts = B.mace_fp32_products(self.g.handle, -1) != B.MACE_PRODUCTS_FP32
+        products = B.mace_fp32_products(self.g.handle, -1)
+        parts = 0 if products == B.MACE_PRODUCTS_FP32 else (3 if self.prec == B.MACE_BF16_RADIAL else 6)
         per_launch = k_launches / steps
         avg_ms = k_ms / max(k_launches, 1)
         if kname in EDGE_PRODUCT:
@@ -247,16 +260,23 @@ class Arm:
                 mf, vf, cb = mf + a, vf + b, cb + c
             mf, vf, cb = mf / per_launch, vf / per_launch, cb / per_launch
             tfl = (mf + vf) / (avg_ms * 1e-3) / 1e12
-            roof = {"bound": "mfma", "achieved": round(tfl, 3), "peak": FP32_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
-                    "frac": round(tfl / FP32_MFMA_PEAK_TFLOPS, 4),
+            # The peak of this mix of work: its radial products at the rate of the
+            # matrix products that carry them, its CG at the vector rate, the
+            # slower of the two pipes alone (what of both goes side by side is
+            # not known in advance)
+            if products == B.MACE_PRODUCTS_FP32:
+                t_m = mf / (FP32_MFMA_PEAK_TFLOPS * 1e12)
+            else:   # BF16 radial: R one product, dR/dr two (da3/dr to 16 bits)
+                bf16 = 1.5 if kname == "tpr_bwd_kernel" else 1.0
+                n = bf16 if self.prec == B.MACE_BF16_RADIAL else SPLIT_PRODUCTS
+                t_m = n * mf / (BF16_MFMA_PEAK_TFLOPS * 1e12)
+            t_v = vf / (FP32_VALU_PEAK_TFLOPS * 1e12)
+            peak = (mf + vf) / max(t_m, t_v) / 1e12
+            roof = {"bound": "valu" if t_v > t_m else "mfma", "achieved": round(tfl, 3), "peak": round(peak, 1),
+                    "unit": "TFLOP/s", "frac": round(tfl / peak, 4),
                     "work": "per edge 2*64*P*K (radial layer, MFMA) + 2K(nnz+mid) (CG, VALU), x2 backward",
                     "mfma_flops_per_launch": int(mf), "valu_flops_per_launch": int(vf),
-                    # MFMA and VALU issue do not overlap on a gfx950 SIMD: the
-                    # ideal time is the sum of the two pipes' times at peak, the
-                    # FP32-accurate radial products running as six BF16 MFMA
-                    # products each (split operands) and the CG on FP32 VALU
-                    "pipe_time_frac": round((6 * mf / (BF16_MFMA_PEAK_TFLOPS * 1e12)
-                                             + vf / (FP32_VALU_PEAK_TFLOPS * 1e12)) / (avg_ms * 1e-3), 4),
+                    "mfma_time_frac": round(t_m / (avg_ms * 1e-3), 4), "valu_time_frac": round(t_v / (avg_ms * 1e-3), 4),
                     "compulsory_bytes_per_launch": int(cb)}
         else:
             byts = hbm_class_bytes(kname, model, self.N, self.E, l0_factored, self.params["n_species"], parts)
