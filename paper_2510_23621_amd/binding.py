@@ -347,7 +347,8 @@ def mace_debug_fused_linears(handle, request: int = -1) -> int:
 
 def mace_fp32_products(handle, request: int = -1) -> int:
     """Select (MACE_PRODUCTS_FP32 / MACE_PRODUCTS_SPLIT_BF16) or, with request < 0,
-    only query the operands of the last radial layer; returns the setting."""
+    only query the operands of the last radial layer and of the FP32 mode's
+    linears; returns the setting."""
     used = ctypes.c_int32(0)
     _check(lib().mace_fp32_products(handle, request, ctypes.byref(used)), "mace_fp32_products")
     return used.value

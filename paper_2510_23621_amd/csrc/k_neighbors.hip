@@ -30,7 +30,7 @@
 //
 // 36,864 periodic atoms (3.18 M edges): 0.23 ms per call (1.66 ms with all 27
 // images of every atom binned and each candidate searched for its cube and
-// gathered through five dependent loads); 1,536 atoms: 93 us (144 us), the
+// gathered through five dependent loads); 1,536 atoms: 94 us (144 us), the
 // launches and the wait for the count.
 #pragma clang fp contract(off)
 
@@ -178,15 +178,19 @@ nl_bin_kernel(int64_t C, const double* __restrict__ pos, NlGraph g0, const NlGra
 }
 
 // Receiver pass, one wave per receiver: WRITE = false counts the edges of
-// receiver i, WRITE = true writes them to [off_i, off_{i+1}) sorted by
-// (sender, S), unless the total exceeds max_edges or a coordinate was bad. Each
-// half-wave takes every second non-empty cube, 32 candidates at a time; pairs
-// that pass the pre-test go to a list in LDS, which takes the exact test 64 at
-// a time. The count pass keeps up to found_cap of each receiver's finds (what the
-// workspace has left over holds), and the write pass searches again only where
-// there are more. A segment is sorted by rank (a candidate's place = the number of
-// candidates of the segment with a lower number), in LDS up to kNlSortCap edges,
-// beyond it through the segment's own output arrays.
+// receiver i, WRITE = true writes them to [off_i, off_{i+1}) sorted by (sender,
+// S), unless the total exceeds max_edges or a coordinate was bad. Each half-wave
+// takes every second non-empty cube, 32 candidates at a time; pairs that pass
+// the pre-test go to a list in LDS, which takes the exact test 64 at a time. The
+// count pass keeps up to found_cap of each receiver's finds, as many as the
+// workspace has left over, and the write pass searches again where there are
+// more: in periodic systems that is room for 249 and more, all of them as a
+// rule; without images, from a few hundred atoms on, 5 to 10, so that those
+// lists are searched twice (512 molecules 151 us per call, 65,536 atoms in one
+// cluster 330; a larger find list was not measured). A segment is sorted by rank
+// (a candidate's place = the number of candidates of the segment with a lower
+// number), in LDS up to kNlSortCap edges, beyond it through the segment's own
+// output arrays.
 constexpr int kNlWaves = 4;        // receivers per block
 constexpr int kNlSortCap = 256;    // edges per receiver sorted through LDS
 constexpr int kNlList = 256;       // pre-test list entries from which it is emptied

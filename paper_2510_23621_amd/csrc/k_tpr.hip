@@ -37,15 +37,21 @@ constexpr int kYPitch = 20;   // Y tile row: 16 floats + 4 (float4-aligned)
 // 128 VGPRs; for l = 2 the W3 slice fills most of the LDS and one 8-wave block
 // runs two per SIMD. Backward: two waves per SIMD at l = 1 and 2 (206 to 240
 // registers), three at l = 0 (in 4-wave blocks; two or four per SIMD were 3 to
-// 7% slower). Both edge products are bound by issue there: per 16-edge tile and
-// channel tile of the l = 2 backward about 2,290 vector instructions (the
-// contraction's multiply-adds are 2,176) of 4 cycles and 408 MFMAs of 16, in
-// 87% of the SIMDs' time at 2.4 GHz; operand rings of other depths change
-// nothing. The MFMA phases raise the wave's priority so that they issue ahead of
-// the other waves' vector work on the SIMD.
-// At 36,864 atoms (K = 128, l = 2, 3.18 M edges): forward 7.46 -> 7.01 ms,
-// backward 18.55 -> 14.9 ms (and no radial backward); at 1,536 atoms (l = 1)
-// 126 -> 100 us and 230 -> 197 us.
+// 7% slower). By the counters (36,864 atoms, K = 128, l = 2) a 16-edge tile and
+// channel tile of the backward takes 2,365 vector instructions (the contraction's
+// multiply-adds are 2,176) and 408 MFMAs of 16 cycles, in 15,400 cycles of its
+// SIMD; the forward 1,371 and 204 in 7,480. The matrix cores work in 42 and 44%
+// of the cycles. A vector instruction of two or more waves takes its SIMD 2.3 to
+// 4.1 cycles, by its form (measured), and a BF16 MFMA keeps it from vector issue
+// for 7 of its 16: at 4 cycles the two together would fill 81 and 93% of the
+// time, and how many instructions take less is not known. Operand rings of other
+// depths changed nothing. Under this load the clock is 1.74 GHz in the backward
+// and 1.80 in the forward, where the sender sum runs at 2.4. The MFMA phases
+// raise the wave's priority so that they issue ahead of the other waves' vector
+// work on the SIMD.
+// At 36,864 atoms (3.18 M edges): forward 7.46 -> 7.07 ms, backward 18.55 ->
+// 15.2 ms (and no radial backward); at 1,536 atoms (l = 1) 126 -> 100 us and
+// 230 -> 204 us.
 template <int LHMAX, bool BWD, int RM = 0>
 struct TprShape {
   static constexpr int waves = BWD && LHMAX == 0 ? 4 : 8;
