@@ -24,10 +24,14 @@ struct Cand {
   double p[3];  // image position, for binning only
 };
 
-inline int64_t bin_key(int64_t bx, int64_t by, int64_t bz) {
-  const int64_t off = 1 << 20;
-  return ((bx + off) << 42) | ((by + off) << 21) | (bz + off);
-}
+// a bin's indices, whole: packed into one word they would fold onto each other
+// from some 10^6 bins off the origin, and an atom would be met in several bins
+using Bin = std::array<int64_t, 3>;
+struct BinHash {
+  size_t operator()(const Bin& b) const noexcept {
+    return ((size_t)b[0] << 42) + ((size_t)b[1] << 21) + (size_t)b[2];   // distinct near the origin
+  }
+};
 
 bool invert3(const double* c, double* inv) {
   double det = c[0] * (c[4] * c[8] - c[5] * c[7]) - c[1] * (c[3] * c[8] - c[5] * c[6]) +
@@ -98,12 +102,12 @@ extern "C" mace_status mace_neighbor_list(int64_t n_atoms, const double* positio
             cand.push_back(cd);
           }
         }
-    std::unordered_map<int64_t, std::vector<int32_t>> bins;
+    std::unordered_map<Bin, std::vector<int32_t>, BinHash> bins;
     bins.reserve(cand.size() * 2);
     for (size_t u = 0; u < cand.size(); ++u) {
-      int64_t b[3];
+      Bin b;
       for (int c = 0; c < 3; ++c) b[c] = (int64_t)std::floor(cand[u].p[c] / bs);
-      bins[bin_key(b[0], b[1], b[2])].push_back((int32_t)u);
+      bins[b].push_back((int32_t)u);
     }
     for (int64_t i = a0; i < a1; ++i) {
       const double* xi = positions + 3 * i;
@@ -112,7 +116,7 @@ extern "C" mace_status mace_neighbor_list(int64_t n_atoms, const double* positio
       for (int dx = -1; dx <= 1; ++dx)
         for (int dy = -1; dy <= 1; ++dy)
           for (int dz = -1; dz <= 1; ++dz) {
-            auto it = bins.find(bin_key(b[0] + dx, b[1] + dy, b[2] + dz));
+            auto it = bins.find(Bin{b[0] + dx, b[1] + dy, b[2] + dz});
             if (it == bins.end()) continue;
             for (int32_t u : it->second) {
               const Cand& cd = cand[u];

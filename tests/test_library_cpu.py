@@ -127,6 +127,18 @@ def test_neighbor_list_empty_and_isolated():
     assert len(s) == 0
 
 
+@pytest.mark.parametrize("origin", [-1e6, 1e6, -3e8, 3e8])
+def test_neighbor_list_far_from_the_origin(origin):
+    """Some 10^6 cutoffs and more off the origin, every edge comes once (the
+    positions are multiples of 2^-7: differences are exact at any origin)."""
+    pos = np.round(np.random.default_rng(3).uniform(0, 1.5, (60, 3)) * 128) / 128
+    near = B.mace_neighbor_list(pos, 0.5)
+    assert np.array_equal(near[0], oracle_nl(pos, 0.5, None, np.zeros(60, np.int32))[0]) and len(near[0]) > 100
+    far = B.mace_neighbor_list(pos + np.array([origin, -origin, origin]), 0.5)
+    for a, b in zip(near, far):
+        assert np.array_equal(a, b)
+
+
 def test_edge_feature_closed_forms_match_oracle():
     rng = np.random.default_rng(0)
     vec = rng.normal(size=(500, 3)).astype(np.float32)
